@@ -339,6 +339,13 @@ struct AttCfg {
   static constexpr int OW = DENSE && DVW ? DVW : DC;  // value (and partial-result) width
   static constexpr int DVB = (OW + 31) / 32;
   static constexpr int DVBW = DVB / VS;               // value blocks per wave
+  // Rescaling of the accumulators (rare): in place where they live in vector registers; through
+  // the wave's LDS slot where there are so many (one wave per SIMD, 128 registers or more) that
+  // the compiler keeps them in accumulation registers, which no VALU instruction may then touch:
+  // in place would move them to vector registers and back in every step (d_c = 512: 4748 us
+  // through LDS, 5000 in place; d_c = 192, peaked scores: a rescale of all eight waves took about
+  // 6 us through LDS and takes under 1 in place).
+  static constexpr bool RESC_LDS = QB * DVBW >= 8;
   static constexpr int KB = BN / 32;       // 32-key blocks per tile
   static constexpr int VOFF = DENSE ? DQKP : 0;  // first V column of a tile row
   // Tile rows have no padding. Rows whose chunk count is a multiple of 16 bank groups (the
@@ -381,7 +388,7 @@ template <int DC, int DR, int QB, int NW, int BN, int WPC, bool DENSE = false, i
 __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const AttendArgs a) {
   using C = AttCfg<DC, DR, QB, NW, BN, DENSE, DVW, VS>;
   __shared__ __attribute__((aligned(16))) uint16_t tile[C::NBUF][C::TILE];
-  __shared__ __attribute__((aligned(16))) float resc[NW][64 * 16];
+  __shared__ __attribute__((aligned(16))) float resc[C::RESC_LDS ? NW : 1][C::RESC_LDS ? 64 * 16 : 4];
   // pair split: partial score tiles, [tile parity][wave][4 chunks][64 lanes][4]
   __shared__ __attribute__((aligned(16))) float xch[VS > 1 ? 2 : 1][VS > 1 ? NW : 1][64 * 16];
 
@@ -399,7 +406,20 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
   // tiles of one row block is a segment with its own partial result.
   const int64_t U = a.units;
   const int G = a.n_wg, T = a.tiles_per_row;
-  int64_t u_begin = (int64_t)blockIdx.x * U / G, u_end = (int64_t)(blockIdx.x + 1) * U / G;
+  // The split needs up to four divisions before the first load can be issued. With units * G below
+  // 2^32 (a.small_units; every shape of ordinary size) they are 32-bit ones; a 64-bit division is
+  // about 150 instructions in a chain.
+  // (Division results come out of vector registers: uniform() keeps them in scalar ones.)
+  auto uniform = [](int64_t v) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return (int64_t)((uint64_t)hi << 32 | lo);
+  };
+  auto udiv = [&](int64_t n, int64_t d) -> int64_t {
+    return a.small_units ? (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)n / (uint32_t)d)
+                         : uniform(floor_div(n, d));
+  };
+  int64_t u_begin, u_end;
   // Weighted split: the per-XCD weights the partition state holds (set by bal_prep_kernel for an
   // adaptive call, left as they are for a frozen one); an adaptive call records each
   // workgroup's duration for the next one.
@@ -409,22 +429,31 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
     bal_weights(a.bal_state, G, bw);
 #pragma unroll
     for (int x = 0; x < 8; ++x) bw[x] = __builtin_amdgcn_readfirstlane(bw[x]);
-    u_begin = bal_start(bw, G, U, blockIdx.x);
-    u_end = bal_start(bw, G, U, blockIdx.x + 1);
+    const int64_t cum = bal_cum(bw, G);
+    u_begin = uniform(floor_div(U * bal_cum(bw, blockIdx.x), cum));
+    u_end = uniform(floor_div(U * bal_cum(bw, blockIdx.x + 1), cum));
     if (a.bal_rec) bal_t0 = __builtin_amdgcn_s_memrealtime();
+  } else {
+    u_begin = udiv((int64_t)blockIdx.x * U, G);
+    u_end = udiv((int64_t)(blockIdx.x + 1) * U, G);
   }
   // Segments are taken last to first: a workgroup's last segment is the head of a row block
   // (keys from 0) and its first the tail of another, so in this order every workgroup walks the
   // keys at about the same position at the same time (all ranges have the same length), and
   // the workgroups of one XCD find most tiles already in its L2.
+  int64_t rbg = udiv(u_end - 1, T);  // the segment's row block; the next segment's is the one before
+  int b = (int)udiv(rbg, a.row_blocks), rb = (int)(rbg - (int64_t)b * a.row_blocks);
   for (int64_t u = u_end; u > u_begin;) {
-  const int64_t rbg = (u - 1) / T;
   const int64_t seg_lo = max(u_begin, rbg * T);
   const int kt0 = (int)(seg_lo - rbg * T);
   const int kt1 = (int)(u - rbg * T);
+  // a segment from the row block's first key is its split 0
+  int split = 0;
+  if (kt0 > 0)
+    split = (int)blockIdx.x -
+            (a.bal_on ? __builtin_amdgcn_readfirstlane(bal_owner_fd(bw, G, U, rbg * T))
+                      : (int)udiv((rbg * T + 1) * G - 1, U));
   u = seg_lo;
-  const int b = (int)(rbg / a.row_blocks), rb = (int)(rbg % a.row_blocks);
-  const int split = (int)blockIdx.x - (a.bal_on ? bal_owner(bw, G, U, rbg * T) : attend_owner(rbg * T, U, G));
   const int vpar = VS > 1 ? wave % VS : 0;  // column half of this wave (pair split)
   const int row0 = rb * C::ROWS + wave / VS * QB * 32;
   const int key_begin = kt0 * BN;
@@ -582,9 +611,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
   };
   // Raise the running max where the scores `s` would exceed it by more than kLazyMax. Each lane
   // sees half of its row's keys; growth on either half sends the wave through the rare path,
-  // where the two halves agree on the new max and the accumulators are rescaled through this
-  // wave's LDS slot (no VALU instruction ever touches them, so they stay in accumulation
-  // registers).
+  // where the two halves agree on the new max and the accumulators are rescaled (see RESC_LDS).
   float own_max[QB];
   auto own_max_of = [&](const f32x16 (&s)[QB][C::KB]) {
 #pragma unroll
@@ -607,7 +634,6 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) grow |= own_max[qb] > m_run[qb] + kLazyMax;
     if (__builtin_amdgcn_ballot_w64(grow) != 0) {
-      f32x16* slot = reinterpret_cast<f32x16*>(&resc[wave][lane * 16]);
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
         const float m_new = fmaxf(m_run[qb], half_swap_max(own_max[qb]));
@@ -616,13 +642,18 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
         l_run[qb] *= alpha;
 #pragma unroll
         for (int d = 0; d < C::DVBW; ++d) {
-          *slot = o[qb][d];
-          asm volatile("" ::: "memory");
-          f32x16 tmp = *slot;
-          tmp *= alpha;
-          *slot = tmp;
-          asm volatile("" ::: "memory");
-          o[qb][d] = *slot;
+          if constexpr (C::RESC_LDS) {
+            f32x16* slot = reinterpret_cast<f32x16*>(&resc[wave][lane * 16]);
+            *slot = o[qb][d];
+            asm volatile("" ::: "memory");
+            f32x16 tmp = *slot;
+            tmp *= alpha;
+            *slot = tmp;
+            asm volatile("" ::: "memory");
+            o[qb][d] = *slot;
+          } else {
+            o[qb][d] *= alpha;
+          }
         }
       }
     }
@@ -773,7 +804,8 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
   if (n_tiles > 0) {
     if (key_begin + BN > key_end) mask_tail(key_begin, s_a);
     own_max_of(s_a);
-    raise_max_if_needed();  // sets the running max from the first tile
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) m_run[qb] = half_swap_max(own_max[qb]);  // nothing to rescale yet
   }
   // tile t lives in buffer t mod 3; the three buffer pointers rotate with the tiles
   uint16_t *pc = tile[0], *pn = tile[1], *ps = tile[2];
@@ -817,6 +849,11 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
   }
   if (!DENSE && stamp_seg == 0) VMLA_STAMP(a, kStampAttend, 13);
   ++stamp_seg;
+  --rbg;
+  if (--rb < 0) {
+    rb = a.row_blocks - 1;
+    --b;
+  }
   }  // segments
   if (!DENSE) VMLA_STAMP_DRAINED(a, kStampAttend, 11);
   if (a.bal_rec && tid == 0)

@@ -668,6 +668,7 @@ AttendArgs attend_args(const videomla_dims* d, const videomla_window* w, int32_t
   a.row_blocks = P.RB;
   a.tiles_per_row = P.T;
   a.units = P.U;
+  a.small_units = P.U < ((int64_t(1) << 32) / P.G);
   a.max_seg = P.max_seg;
   set_balance(a, P, ws, L, o);
   const double scale = d->softmax_scale > 0.f ? (double)d->softmax_scale
@@ -700,6 +701,7 @@ AttendArgs head_args(const videomla_dims* d, const videomla_window* w, int32_t b
   a.row_blocks = P.RB;
   a.tiles_per_row = P.T;
   a.units = P.U;
+  a.small_units = P.U < ((int64_t(1) << 32) / P.G);
   a.max_seg = P.max_seg;
   set_balance(a, P, ws, L, o);
   const double dk = materialized ? (double)(d->d_nope + d->d_rope) : (double)d->d_v;

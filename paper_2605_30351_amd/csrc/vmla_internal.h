@@ -105,6 +105,7 @@ struct AttendArgs {
   int32_t row_blocks;      // row blocks per batch element
   int32_t tiles_per_row;   // T = ceil(n_valid / keys per tile)
   int64_t units;           // U = batch * row_blocks * T
+  int32_t small_units;     // U * G < 2^32: the attention kernel's split in 32-bit arithmetic
   int32_t max_seg;         // partial-result slots the workspace holds
   float qscale;            // softmax scale * log2(e), folded into the absorbed query
   // Weighted partition (optional): the state area of kBalSlot words in the workspace (see bal_*

@@ -322,30 +322,20 @@ constexpr float kLazyMax = 8.0f;
 // width, DR = 0, DVW = value width, 0 meaning DC): a tile row is [K_h | V_h] of one head, the
 // scores contract over K_h and V is the rest (the dense comparator: 128 | 128; the materialized
 // form: [W_UK,h c ; k^R] | W_UV,h c = 128 | 128 or 160 | 128).
-//
-// Pair split (VS = 2, latent rows only): the waves of a pair share their 32 query rows. Each
-// contracts the scores over its half of the [c_kv | k_r] columns, the two partial score tiles
-// are exchanged through LDS at the step's barrier and summed (in the same order of operands on
-// both sides, so both hold bitwise identical scores, running max and sum), and each wave
-// accumulates the PV product for its half of the value columns. This halves the accumulator and
-// query registers per wave, for latent widths whose 32 x d_c fp32 accumulators would not fit
-// one wave, without computing any score twice.
-template <int DC, int DR, int QB, int NW, int BN, bool DENSE = false, int DVW = 0, int VS = 1>
+template <int DC, int DR, int QB, int NW, int BN, bool DENSE = false, int DVW = 0>
 struct AttCfg {
   static constexpr int DQK = DC + DR;
   static constexpr int DQKP = (DQK + 15) / 16 * 16;
   static constexpr int KSTEPS = DQKP / 16;
-  static constexpr int NSH = KSTEPS / VS;  // score steps of one wave
   static constexpr int OW = DENSE && DVW ? DVW : DC;  // value (and partial-result) width
   static constexpr int DVB = (OW + 31) / 32;
-  static constexpr int DVBW = DVB / VS;               // value blocks per wave
   // Rescaling of the accumulators (rare): in place where they live in vector registers; through
   // the wave's LDS slot where there are so many (one wave per SIMD, 128 registers or more) that
   // the compiler keeps them in accumulation registers, which no VALU instruction may then touch:
   // in place would move them to vector registers and back in every step (d_c = 512: 4748 us
   // through LDS, 5000 in place; d_c = 192, peaked scores: a rescale of all eight waves took about
   // 6 us through LDS and takes under 1 in place).
-  static constexpr bool RESC_LDS = QB * DVBW >= 8;
+  static constexpr bool RESC_LDS = QB * DVB >= 8;
   static constexpr int KB = BN / 32;       // 32-key blocks per tile
   static constexpr int VOFF = DENSE ? DQKP : 0;  // first V column of a tile row
   // Tile rows have no padding. Rows whose chunk count is a multiple of 16 bank groups (the
@@ -356,9 +346,7 @@ struct AttCfg {
   // enumeration on the host for every layout instantiated here).
   static constexpr int STRIDE = DENSE ? DQKP + OW : DQKP;
   static constexpr int NT = NW * 64;
-  static constexpr int ROWS = NW / VS * QB * 32;
-  static_assert(VS == 1 || (VS == 2 && !DENSE && DVB % VS == 0 && NW % VS == 0 &&
-                            KSTEPS % VS == 0 && QB == 1 && BN == 32), "pair split");
+  static constexpr int ROWS = NW * QB * 32;
   static constexpr int OCT_C = DC / 8, OCT_R = DR / 8;
   static constexpr int CPR = STRIDE / 8;          // 16-byte chunks per tile row
   static constexpr int NDMA = BN * CPR / 64;      // 1 KB direct-to-LDS loads per tile
@@ -383,14 +371,11 @@ struct AttCfg {
   }
 };
 
-template <int DC, int DR, int QB, int NW, int BN, int WPC, bool DENSE = false, int DVW = 0,
-          int VS = 1>
+template <int DC, int DR, int QB, int NW, int BN, int WPC, bool DENSE = false, int DVW = 0>
 __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const AttendArgs a) {
-  using C = AttCfg<DC, DR, QB, NW, BN, DENSE, DVW, VS>;
+  using C = AttCfg<DC, DR, QB, NW, BN, DENSE, DVW>;
   __shared__ __attribute__((aligned(16))) uint16_t tile[C::NBUF][C::TILE];
   __shared__ __attribute__((aligned(16))) float resc[C::RESC_LDS ? NW : 1][C::RESC_LDS ? 64 * 16 : 4];
-  // pair split: partial score tiles, [tile parity][wave][4 chunks][64 lanes][4]
-  __shared__ __attribute__((aligned(16))) float xch[VS > 1 ? 2 : 1][VS > 1 ? NW : 1][64 * 16];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -454,8 +439,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
             (a.bal_on ? __builtin_amdgcn_readfirstlane(bal_owner_fd(bw, G, U, rbg * T))
                       : (int)udiv((rbg * T + 1) * G - 1, U));
   u = seg_lo;
-  const int vpar = VS > 1 ? wave % VS : 0;  // column half of this wave (pair split)
-  const int row0 = rb * C::ROWS + wave / VS * QB * 32;
+  const int row0 = rb * C::ROWS + wave * QB * 32;
   const int key_begin = kt0 * BN;
   const int key_end = min(a.n_valid, kt1 * BN);
   const int n_tiles = kt1 - kt0;
@@ -503,27 +487,25 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
   }
 
 
-  // queries of this wave, B-operand layout: lane holds row l32, dims ks*16 + 8g .. +8 (of the
-  // wave's NSH score steps, which start at step vpar * NSH)
-  bf16x8 q[QB][C::NSH];
+  // queries of this wave, B-operand layout: lane holds row l32, dims ks*16 + 8g .. +8
+  bf16x8 q[QB][C::KSTEPS];
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     const int r = row0 + qb * 32 + l32;
-    const uint16_t* src = a.qcat + ((size_t)b * rows_b + (r < rows_b ? r : 0)) * C::DQKP +
-                          vpar * C::NSH * 16;
+    const uint16_t* src = a.qcat + ((size_t)b * rows_b + (r < rows_b ? r : 0)) * C::DQKP;
 #pragma unroll
-    for (int ks = 0; ks < C::NSH; ++ks)
+    for (int ks = 0; ks < C::KSTEPS; ++ks)
       q[qb][ks] = as_bf16x8(r < rows_b ? ldg16(src + ks * 16 + 8 * g) : zero);
   }
 
-  f32x16 o[QB][C::DVBW];
+  f32x16 o[QB][C::DVB];
   float m_run[QB], l_run[QB];
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     m_run[qb] = kNegInf;
     l_run[qb] = 0.f;
 #pragma unroll
-    for (int d = 0; d < C::DVBW; ++d) o[qb][d] = f32x16{};
+    for (int d = 0; d < C::DVB; ++d) o[qb][d] = f32x16{};
   }
 
   auto dma_tile = [&](int k0, uint16_t* buf) {
@@ -542,13 +524,9 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
   // K operand of step ks: row l32 (+32 kb), chunk 2 ks + g, i.e. C::at(). Latent: the XOR folded
   // into one of two per-lane bases (ks even / odd) so that ks and kb become immediate offsets;
   // dense: one offset per step (its 4-bit XOR reaches every chunk of a group).
-  // With the pair split, local step ks is global step vpar * NSH + ks, whose parity picks the base.
   const int hk = (l32 >> 2) & 3;
-  const int koff_ev = l32 * C::STRIDE + ((g ^ hk) << 3);
-  const int koff_od = l32 * C::STRIDE + (((2 + g) ^ hk) << 3) - 16;
-  const bool kflip = (vpar * C::NSH) & 1;
-  const int koff_e = (kflip ? koff_od : koff_ev) + vpar * C::NSH * 16;
-  const int koff_o = (kflip ? koff_ev : koff_od) + vpar * C::NSH * 16;
+  const int koff_e = l32 * C::STRIDE + ((g ^ hk) << 3);
+  const int koff_o = l32 * C::STRIDE + (((2 + g) ^ hk) << 3) - 16;
   int koff_d[DENSE ? C::KSTEPS : 1];
   if constexpr (DENSE) {
 #pragma unroll
@@ -565,36 +543,11 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) s[qb][kb] = f32x16{};
 #pragma unroll
-      for (int ks = 0; ks < C::NSH; ++ks) {
+      for (int ks = 0; ks < C::KSTEPS; ++ks) {
         const bf16x8 k = as_bf16x8(*reinterpret_cast<const u32x4*>(
             &buf[koff(ks) + kb * 32 * C::STRIDE]));
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) s[qb][kb] = mfma32(k, q[qb][ks], s[qb][kb]);
-      }
-    }
-  };
-  // Pair split: publish this wave's partial scores of tile parity `par` (before a barrier), then
-  // (after it) add the partner's. Chunk j of lane l sits at (64 j + l) * 4 floats, so every
-  // 16-byte access of a wave covers consecutive addresses.
-  auto xch_put = [&](int par, const f32x16 (&s)[QB][C::KB]) {
-    if constexpr (VS > 1) {
-      float* dst = &xch[par][wave][lane * 4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        *reinterpret_cast<f32x4*>(dst + 256 * j) =
-            f32x4{s[0][0][4 * j], s[0][0][4 * j + 1], s[0][0][4 * j + 2], s[0][0][4 * j + 3]};
-    }
-  };
-  auto xch_add = [&](int par, f32x16 (&s)[QB][C::KB]) {
-    if constexpr (VS > 1) {
-      const float* src = &xch[par][wave ^ 1][lane * 4];
-      // vpar 0 computes mine + partner's and vpar 1 partner's + mine: the same sum either way
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(src + 256 * j);
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          s[0][0][4 * j + i] = vpar == 0 ? s[0][0][4 * j + i] + v[i] : v[i] + s[0][0][4 * j + i];
       }
     }
   };
@@ -641,7 +594,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
         m_run[qb] = m_new;
         l_run[qb] *= alpha;
 #pragma unroll
-        for (int d = 0; d < C::DVBW; ++d) {
+        for (int d = 0; d < C::DVB; ++d) {
           if constexpr (C::RESC_LDS) {
             f32x16* slot = reinterpret_cast<f32x16*>(&resc[wave][lane * 16]);
             *slot = o[qb][d];
@@ -663,10 +616,8 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
   // column tr_col (+32 d); rows 4g.. have swizzle g, rows 4g+8.. have g+2, for every kk
   const int tr_row = (lane & 15) >> 2;
   const int tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-  // (the latent swizzle permutes chunks within 32-column groups, so a whole number of 32-column
-  // blocks is a plain offset: this wave's value half starts vpar * DVBW blocks in)
-  const int vofs_lo = C::at(4 * g + tr_row, C::VOFF + tr_col) + vpar * C::DVBW * 32;
-  const int vofs_hi = C::at(4 * g + tr_row + 8, C::VOFF + tr_col) + vpar * C::DVBW * 32;
+  const int vofs_lo = C::at(4 * g + tr_row, C::VOFF + tr_col);
+  const int vofs_hi = C::at(4 * g + tr_row + 8, C::VOFF + tr_col);
   // dense: the 4-bit XOR also permutes the 32-column blocks d, so one offset per (half, d)
   int vofs_d[2][DENSE ? C::DVB : 1];
   if constexpr (DENSE) {
@@ -692,8 +643,8 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
     // so the wave's LDS traffic and VALU work are spread evenly under its MFMAs.
     dma_tile(kbase + 2 * BN, stg);  // buffer of tile t-1, free since the last barrier
     static_assert(C::KB == 1, "the step is laid out for 32-key tiles");
-    constexpr int NS = C::NSH;
-    constexpr int NPV = 2 * C::DVBW;  // PV operand reads per tile (each feeds QB MFMAs)
+    constexpr int NS = C::KSTEPS;
+    constexpr int NPV = 2 * C::DVB;  // PV operand reads per tile (each feeds QB MFMAs)
     constexpr int NSLOT = NS > NPV + 2 ? NS : NPV + 2;
     constexpr int NSM = NS < 4 ? NS : 4;  // slots carrying the softmax; pairs 0-3 precede PV
     auto kread = [&](int ks) {
@@ -702,7 +653,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
     const lds_u16* vlo = as_lds(cur) + vofs_lo;
     const lds_u16* vhi = as_lds(cur) + vofs_hi;
     auto vread = [&](int j) {  // A operand of PV MFMA j: kk = j / DVBW, d = j % DVBW
-      const int kk = j / C::DVBW, d = j % C::DVBW;
+      const int kk = j / C::DVB, d = j % C::DVB;
       if constexpr (DENSE)
         return join_bf16x8(lds_read_tr(as_lds(cur) + vofs_d[0][d] + kk * 16 * C::STRIDE),
                            lds_read_tr(as_lds(cur) + vofs_d[1][d] + kk * 16 * C::STRIDE));
@@ -752,7 +703,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
           for (int p = ks * 8 / NSM; p < (ks + 1) * 8 / NSM; ++p) sm_pair(qb, p);
       }
       if (j >= 0 && j < NPV) {
-        const int kk = j / C::DVBW, d = j % C::DVBW;
+        const int kk = j / C::DVB, d = j % C::DVB;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
           const bf16x8 pb = as_bf16x8(kk == 0 ? u32x4{pk[qb][0], pk[qb][1], pk[qb][2], pk[qb][3]}
@@ -767,7 +718,6 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
       s_nxt[qb][0] = acc[qb];
       l_run[qb] = lsum[qb];
     }
-    xch_put((t + 1) & 1, s_nxt);
     // phase stamps: the stream's end is read here and stored after the barrier, so that the
     // wait below has no stamp store to drain
     const bool stamped = !DENSE && stamp_step >= 200 && stamp_step < 204;
@@ -779,7 +729,6 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
       VMLA_STAMP_AT(a, kStampAttend, 2 + 2 * (stamp_step - 200), stream_end);
     }
     ++stamp_step;
-    xch_add((t + 1) & 1, s_nxt);
     if (kbase + 2 * BN > key_end) mask_tail(kbase + BN, s_nxt);  // only near the split's end
     own_max_of(s_nxt);
     raise_max_if_needed();
@@ -796,11 +745,6 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
 
   f32x16 s_a[QB][C::KB], s_b[QB][C::KB];
   if (n_tiles > 0) scores(tile[0], s_a);
-  if constexpr (VS > 1) {
-    if (n_tiles > 0) xch_put(0, s_a);
-    __syncthreads();
-    if (n_tiles > 0) xch_add(0, s_a);
-  }
   if (n_tiles > 0) {
     if (key_begin + BN > key_end) mask_tail(key_begin, s_a);
     own_max_of(s_a);
@@ -832,16 +776,16 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
     const size_t grow_i = (size_t)b * rows_b + r;
     float* op = a.o_part + ((size_t)split * total_rows + grow_i) * C::OW;
 #pragma unroll
-    for (int d = 0; d < C::DVBW; ++d)
+    for (int d = 0; d < C::DVB; ++d)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int c = (vpar * C::DVBW + d) * 32 + 8 * i + 4 * g;
+        const int c = d * 32 + 8 * i + 4 * g;
         if (c < C::OW) {
           const f32x4 v = {o[qb][d][4 * i], o[qb][d][4 * i + 1], o[qb][d][4 * i + 2], o[qb][d][4 * i + 3]};
           *reinterpret_cast<f32x4*>(op + c) = v;
         }
       }
-    if (g == 0 && vpar == 0) {
+    if (g == 0) {
       float* ml = a.ml_part + ((size_t)split * total_rows + grow_i) * 2;
       ml[0] = m_run[qb];
       ml[1] = l_tot;
@@ -1097,27 +1041,26 @@ __global__ __launch_bounds__(NW * 64) void out_proj_kernel(const AttendArgs a) {
 template <int DC, int DR> struct AttShape;
 // WPC = resident workgroups per CU (the grid is WPC workgroups per CU). Two 4-wave workgroups
 // per CU measured 6% slower than one 8-wave workgroup at the Wan shape.
-template <> struct AttShape<192, 32> { static constexpr int QB = 1, NW = 8, BN = 32, WPC = 1, VS = 1; };
-template <> struct AttShape<16, 8> { static constexpr int QB = 1, NW = 4, BN = 32, WPC = 1, VS = 1; };
+template <> struct AttShape<192, 32> { static constexpr int QB = 1, NW = 8, BN = 32, WPC = 1; };
+template <> struct AttShape<16, 8> { static constexpr int QB = 1, NW = 4, BN = 32, WPC = 1; };
 // the latent widths of the paper's d_c sweep (Table 5), with the same 32-wide RoPE key
-template <> struct AttShape<64, 32> { static constexpr int QB = 1, NW = 8, BN = 32, WPC = 1, VS = 1; };
-template <> struct AttShape<128, 32> { static constexpr int QB = 1, NW = 8, BN = 32, WPC = 1, VS = 1; };
+template <> struct AttShape<64, 32> { static constexpr int QB = 1, NW = 8, BN = 32, WPC = 1; };
+template <> struct AttShape<128, 32> { static constexpr int QB = 1, NW = 8, BN = 32, WPC = 1; };
 // d_c = 256: 32 rows x 256 fp32 accumulators per wave need one wave per SIMD (8 waves spill)
-template <> struct AttShape<256, 32> { static constexpr int QB = 1, NW = 4, BN = 32, WPC = 1, VS = 1; };
-// d_c = 512: wave pairs split the score contraction and the value columns (pair split), one
-// wave per SIMD
-template <> struct AttShape<512, 32> { static constexpr int QB = 1, NW = 4, BN = 32, WPC = 1, VS = 2; };
+template <> struct AttShape<256, 32> { static constexpr int QB = 1, NW = 4, BN = 32, WPC = 1; };
 
-// Every (d_c, d_rope) the latent path is instantiated for.
-#define VMLA_LATENT_SHAPES(X) X(192, 32) X(16, 8) X(64, 32) X(128, 32) X(256, 32) X(512, 32)
+// Every (d_c, d_rope) the latent path is instantiated for: the shapes above, and d_c = 512, whose
+// 32 x 512 fp32 accumulators do not fit one wave (k_attend_wide.hip).
+#define VMLA_NARROW_SHAPES(X) X(192, 32) X(16, 8) X(64, 32) X(128, 32) X(256, 32)
+#define VMLA_LATENT_SHAPES(X) VMLA_NARROW_SHAPES(X) X(512, 32)
 
 template <int DC, int DR>
 hipError_t launch_attend_t(const AttendArgs& a, hipStream_t s) {
   using S = AttShape<DC, DR>;
-  using C = AttCfg<DC, DR, S::QB, S::NW, S::BN, false, 0, S::VS>;
+  using C = AttCfg<DC, DR, S::QB, S::NW, S::BN>;
   const dim3 grid(a.n_wg);
-  hipLaunchKernelGGL((latent_attend_kernel<DC, DR, S::QB, S::NW, S::BN, S::WPC, false, 0, S::VS>),
-                     grid, dim3(C::NT), 0, s, a);
+  hipLaunchKernelGGL((latent_attend_kernel<DC, DR, S::QB, S::NW, S::BN, S::WPC>), grid,
+                     dim3(C::NT), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1157,8 +1100,7 @@ hipError_t launch_mat_attend(const AttendArgs& a, hipStream_t s) {
 }
 
 template <int DC, int DR> using ShapeCfg =
-    AttCfg<DC, DR, AttShape<DC, DR>::QB, AttShape<DC, DR>::NW, AttShape<DC, DR>::BN, false, 0,
-           AttShape<DC, DR>::VS>;
+    AttCfg<DC, DR, AttShape<DC, DR>::QB, AttShape<DC, DR>::NW, AttShape<DC, DR>::BN>;
 
 bool latent_attend_supported(int d_c, int d_rope) {
 #define X(DC, DR) if (d_c == DC && d_rope == DR) return true;
@@ -1169,23 +1111,23 @@ bool latent_attend_supported(int d_c, int d_rope) {
 
 int latent_attend_rows_per_block(int d_c, int d_rope) {
 #define X(DC, DR) if (d_c == DC && d_rope == DR) return ShapeCfg<DC, DR>::ROWS;
-  VMLA_LATENT_SHAPES(X)
+  VMLA_NARROW_SHAPES(X)
 #undef X
-  return 0;
+  return latent_attend_supported(d_c, d_rope) ? kWideRows : 0;
 }
 
 int latent_attend_keys_per_tile(int d_c, int d_rope) {
 #define X(DC, DR) if (d_c == DC && d_rope == DR) return AttShape<DC, DR>::BN;
-  VMLA_LATENT_SHAPES(X)
+  VMLA_NARROW_SHAPES(X)
 #undef X
-  return 0;
+  return latent_attend_supported(d_c, d_rope) ? kWideKeys : 0;
 }
 
 int latent_attend_wgs_per_cu(int d_c, int d_rope) {
 #define X(DC, DR) if (d_c == DC && d_rope == DR) return AttShape<DC, DR>::WPC;
-  VMLA_LATENT_SHAPES(X)
+  VMLA_NARROW_SHAPES(X)
 #undef X
-  return 0;
+  return latent_attend_supported(d_c, d_rope) ? 1 : 0;
 }
 
 size_t q_absorb_lds_bytes(int d_c, int d_rope, int d_nope) {
@@ -1227,8 +1169,9 @@ hipError_t launch_bal_prep(const AttendArgs& a, hipStream_t s) {
 
 hipError_t launch_latent_attend(const AttendArgs& a, hipStream_t s) {
 #define X(DC, DR) if (a.d_c == DC && a.d_rope == DR) return launch_attend_t<DC, DR>(a, s);
-  VMLA_LATENT_SHAPES(X)
+  VMLA_NARROW_SHAPES(X)
 #undef X
+  if (a.d_c == 512 && a.d_rope == 32) return launch_latent_attend_wide(a, s);
   return hipErrorInvalidValue;
 }
 

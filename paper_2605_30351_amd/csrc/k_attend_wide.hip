@@ -31,8 +31,6 @@
 // 4 (r mod 4) hit 16 different bank groups; h(r) = (r / 4) mod 4 gave two lanes per group
 // (conflicts in 37% of the LDS cycles, now 6%). The 4-row transpose reads of the PV MFMA hit 16
 // different groups with either.
-#include <type_traits>
-
 #include "vmla_device.h"
 
 namespace vmla {
@@ -45,19 +43,6 @@ constexpr float kLazyMaxW = 8.0f;  // the running max is raised by more than thi
 // accumulator element i of lane l is D[4(l/16) + i][l%16].
 __device__ __forceinline__ f32x4 mfma16w(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-// Direct global-to-LDS load as lds_dma16, to LDS address lds_base + LDS_OFF, from a scalar base and
-// the lane offset min(off, lim) in bytes: three instructions (a lone wave on its SIMD pays an issue
-// cycle for each), the minimum also being the wait state between the write of m0 and its use.
-template <int LDS_OFF>
-__device__ __forceinline__ void lds_dma16_min(const void* base, uint32_t off, uint32_t lim,
-                                              uint32_t lds_base) {
-  uint32_t tmp;
-  asm volatile("s_add_u32 m0, %4, %5\n\tv_min_u32 %0, %1, %2\n\tglobal_load_lds_dwordx4 %0, %3"
-               : "=&v"(tmp)
-               : "v"(off), "v"(lim), "s"(base), "s"(lds_base), "n"(LDS_OFF)
-               : "memory", "m0", "scc");
 }
 
 // s_waitcnt with only the LDS counter constrained (gfx9 encoding).
@@ -85,15 +70,6 @@ __device__ __forceinline__ float quad_max(float v) {
 __device__ __forceinline__ float quad_sum(float v) {
   auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return half_swap_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
-}
-
-// f(0), f(1), .. f(N - 1) with constant arguments.
-template <int N, class F>
-__device__ __forceinline__ void for_const(F&& f) {
-  if constexpr (N > 0) {
-    for_const<N - 1>(f);
-    f(std::integral_constant<int, N - 1>{});
-  }
 }
 
 template <int DC, int DR>

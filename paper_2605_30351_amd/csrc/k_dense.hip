@@ -12,6 +12,7 @@
 //   (the attention itself is latent_attend_kernel with the dense tile layout)
 //   dense_merge        merges the key splits exactly and writes out[b][n][h]
 #include "vmla_device.h"
+#include "vmla_gemm.h"
 
 namespace vmla {
 namespace {
@@ -146,6 +147,126 @@ __global__ __launch_bounds__(256, 1) void dense_cache_write_kernel(const DenseWr
       *reinterpret_cast<bf16x4*>(dst + (size_t)h * 2 * DH + (is_k ? 0 : DH) + ch) = to_bf16x4(fv);
     }
   if (a.slots && b == 0 && blockIdx.y == 0 && g == 0) a.slots[n] = (int32_t)slot;
+}
+
+// ---------------------------------------------------------------------------------------------
+// dense_cache_write_wide: the same product with a 256-token x 256-output tile per workgroup (8
+// waves of 64 x 128), the tokens flat over the batch. Tiles are numbered token-block-major and
+// dealt to the XCDs in contiguous ranges, so that the tiles of an XCD's L2 share their token rows
+// and the weights.
+// What bounds it: the 128 x 128 tile of the kernel above reads 1.25 KB of LDS per MFMA, more than
+// the LDS delivers in its 32 cycles, takes in twice the bytes per product, and its four waves wait
+// for every stage together. Here an MFMA takes 0.75 KB, and every operand is read a step ahead.
+// 18,720 tokens x 3,072 outputs x 1,536: 307 us with the small tiles, 202 now (875 TFLOP/s; 888
+// tiles are 3.5 rounds of 256). With the MFMAs alone 123 us, without the tile loads 161, without
+// the LDS reads 174, without the epilogue 165: the parts share the chip's power more than its
+// cycles. Four waves of 128 x 128 (half the LDS bytes per MFMA): 266 us, 64-column stages with two
+// in flight: 227.
+// The epilogue takes 32 of each wave's 64 tokens at a time: the (cos, sin) of those 128 tokens and
+// every RoPE pair into LDS (K tiles), the rotated bf16 rows into an LDS tile per wave, and 16-byte
+// chunks of whole rows from there to the ring.
+// ---------------------------------------------------------------------------------------------
+using DwTile = GemmTile<4, 2, 2, 4, 32, 4>;
+constexpr int kDwCs = kDwMaxPairs + 1;                       // (cos, sin) row stride, padded
+constexpr int kDwOs = DwTile::MO * 32 + 8;                   // output tile row stride (elements)
+constexpr size_t kDwOutBytes = (size_t)DwTile::NW * 32 * kDwOs * 2;
+constexpr size_t kDwStageBytes = (size_t)DwTile::ST * DwTile::STAGE * 2;
+constexpr size_t kDwEpiBytes = kDwOutBytes + (size_t)DwTile::WT * 32 * kDwCs * 8;
+constexpr size_t kDwLdsBytes = kDwStageBytes > kDwEpiBytes ? kDwStageBytes : kDwEpiBytes;
+constexpr int kDwWideHead = 128;  // compile-time head width of the usual instantiation
+
+template <bool D128>
+__global__ __launch_bounds__(DwTile::NT, 1) void dense_cache_write_wide_kernel(const DenseWriteArgs a) {
+  using P = DwTile;
+  __shared__ __attribute__((aligned(16))) char smem[kDwLdsBytes];
+  __shared__ int64_t ring_row[DwTile::TT];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wt = wave % P::WT, wo = wave / P::WT;
+  const int g = lane >> 5, l32 = lane & 31;
+  const int DH = D128 ? kDwWideHead : a.d_head;
+  const int dm = a.d_model, H = a.n_heads, n_tok = a.geo.chunk_tokens;
+  const int hd = H * DH, N = 2 * hd;
+  const int M = a.batch * n_tok;  // < 2^31 (checked by the launcher)
+  const int nty = (N + P::TO - 1) / P::TO, Gr = gridDim.x, id = blockIdx.x;
+  const int xcd = id & 7, L = xcd * (Gr >> 3) + min(xcd, Gr & 7) + (id >> 3);
+  const int n0 = L / nty * P::TT, o0 = L % nty * P::TO;
+
+  // ring row (and slot) of every token of the tile, once: the divisions are a chain of hundreds of
+  // instructions (published by the barriers of the tile loop)
+  if (tid < P::TT) {
+    const int t = min(n0 + tid, M - 1), b = t / n_tok, n = t - b * n_tok;
+    const int64_t slot = ring_slot(a.geo, token_pos(a.geo, n));
+    ring_row[tid] = (int64_t)b * a.geo.ring_tokens + slot;
+    if (a.slots && b == 0 && o0 == 0) a.slots[n] = (int32_t)slot;
+  }
+  f32x16 acc[P::NB][P::MO];
+  P::run(
+      reinterpret_cast<uint16_t*>(smem), dm / P::KC, dm,
+      [&](int r) {  // rows past the end repeat the last one; their results are not stored
+        if (r < P::TT) {
+          const int t = min(n0 + r, M - 1);
+          return GemmRows{a.x + (size_t)t * dm, M - 1 - t};
+        }
+        const int o = min(o0 + r - P::TT, N - 1);  // hd % 64 == 0: a group is all K or all V rows
+        return o < hd ? GemmRows{a.w_k + (size_t)o * dm, hd - 1 - o}
+                      : GemmRows{a.w_v + (size_t)(o - hd) * dm, N - 1 - o};
+      },
+      [](int, bf16x8) {}, acc);
+
+  uint16_t* ot = reinterpret_cast<uint16_t*>(smem) + wave * 32 * kDwOs;
+  f32x2* cs = reinterpret_cast<f32x2*>(smem + kDwOutBytes);
+  const int npair = DH / 2, ob = o0 + wo * P::MO * 32;  // first output of this wave
+  auto flat_pos = [&](int t) { return token_pos(a.geo, t % n_tok); };
+#pragma unroll
+  for (int p = 0; p < P::NB; ++p) {
+    __syncthreads();  // the stages, or the pass before, are no longer read
+    if (o0 < hd) {
+      // wave w: RoPE pairs w, w + 8, .. (uniform: scalar table reads), lanes: two tokens each
+      TokenPos tp[P::WT / 2];
+#pragma unroll
+      for (int k = 0; k < P::WT / 2; ++k) {
+        const int x = lane + 64 * k;  // token block x / 32, token x mod 32 of its current half
+        tp[k] = flat_pos(min(n0 + (x >> 5) * P::NB * 32 + p * 32 + (x & 31), M - 1));
+      }
+      for (int pr = wave; pr < npair; pr += P::NW) {
+        const RopePair rp = rope_pair(a.rope, __builtin_amdgcn_readfirstlane(pr));
+#pragma unroll
+        for (int k = 0; k < P::WT / 2; ++k) cs[(lane + 64 * k) * kDwCs + pr] = rope_cos_sin(rp, tp[k]);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < P::MO; ++m)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int o = ob + m * 32 + 8 * i + 4 * g;
+        float v[4] = {acc[p][m][4 * i], acc[p][m][4 * i + 1], acc[p][m][4 * i + 2], acc[p][m][4 * i + 3]};
+        if (o < hd) {
+          const f32x2* row = cs + (wt * 32 + l32) * kDwCs + o % DH / 2;
+          rotate_by(row[0], v[0], v[1]);
+          rotate_by(row[1], v[2], v[3]);
+        }
+        const f32x4 fv = {v[0], v[1], v[2], v[3]};
+        *reinterpret_cast<bf16x4*>(&ot[l32 * kDwOs + m * 32 + 8 * i + 4 * g]) = to_bf16x4(fv);
+      }
+    // the wave's own tile: its LDS operations take effect in program order
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    constexpr int CPR = P::MO * 32 / 8, RPI = 64 / CPR;  // chunks per row, rows per store
+    const int ch = lane % CPR, o = ob + ch * 8;          // d_head % 8 == 0: a chunk is one head's
+    const bool is_k = o < hd;
+    const int oo = is_k ? o : o - hd;
+    const size_t col = (size_t)(oo / DH) * 2 * DH + (is_k ? 0 : DH) + oo % DH;
+#pragma unroll
+    for (int it = 0; it < 32 / RPI; ++it) {
+      const int tr = it * RPI + lane / CPR, t = n0 + (wt * P::NB + p) * 32 + tr;
+      if (t < M && o < N)
+        stg16(a.kv + (size_t)ring_row[t - n0] * N + col,
+              *reinterpret_cast<const u32x4*>(&ot[tr * kDwOs + ch * 8]));
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -299,6 +420,22 @@ __global__ __launch_bounds__(256) void dense_merge_kernel(const AttendArgs a) {
 
 hipError_t launch_dense_cache_write(const DenseWriteArgs& a, hipStream_t s) {
   // validated by the caller: d_model % 64 == 0, (2 H d_head) % 128 == 0, d_head even
+  const int64_t M = (int64_t)a.batch * a.geo.chunk_tokens, N = 2LL * a.n_heads * a.d_head;
+  const int64_t wide = (M + DwTile::TT - 1) / DwTile::TT * ((N + DwTile::TO - 1) / DwTile::TO);
+  const int64_t small = (int64_t)a.batch * ((a.geo.chunk_tokens + kDwTok - 1) / kDwTok) * (N / kDwOut);
+  // Rounds of one workgroup per compute unit. A round of wide tiles (four times the work) takes
+  // about as long as two of the small ones: 40 to 54 us a round, the fuller the longer, against 25
+  // for one and 20 for each further one at d_model = 1536, 27 to 32 against 18 and 13 at 768
+  // (2 against 1 rounds: 40.2 against 45.2 us at 1,560 tokens x 12 heads, 4 against 1: 83.6
+  // against 52.3 at 3,120 x 16). d_head % 8: the stores' 16-byte chunks stay inside a head.
+  auto rounds = [&](int64_t tiles) { return (tiles + a.n_cu - 1) / a.n_cu; };
+  if (a.d_head % 8 == 0 && a.d_head / 2 <= kDwMaxPairs && rounds(small) > 2 * rounds(wide) &&
+      M + DwTile::TT < (1LL << 31) && wide < (1LL << 31)) {
+    const dim3 grid((unsigned)wide), block(DwTile::NT);
+    if (a.d_head == kDwWideHead) hipLaunchKernelGGL(dense_cache_write_wide_kernel<true>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(dense_cache_write_wide_kernel<false>, grid, block, 0, s, a);
+    return hipGetLastError();
+  }
   const dim3 grid((a.geo.chunk_tokens + kDwTok - 1) / kDwTok, 2 * a.n_heads * a.d_head / kDwOut,
                   a.batch);
   hipLaunchKernelGGL(dense_cache_write_kernel, grid, dim3(256), 0, s, a);

@@ -872,6 +872,7 @@ int videomla_dense_cache_write(const videomla_dims* d, const videomla_window* w,
   a.batch = batch; a.d_model = d->d_model; a.n_heads = d->n_heads; a.d_head = d->d_v;
   a.geo = make_geo(d, w);
   a.rope = make_dense_rope(d);
+  a.n_cu = device_cu_count();
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const hipError_t e = launch_dense_cache_write(a, s);
   if (e != hipSuccess) return hip_fail(e, "dense_cache_write");

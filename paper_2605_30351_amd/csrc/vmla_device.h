@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "vmla_internal.h"
 
 namespace vmla {
@@ -64,6 +66,36 @@ __device__ __forceinline__ void lds_dma16(const uint16_t* gptr, uint32_t lds_bas
                :
                : "v"(gptr), "s"(lds_base)
                : "memory", "m0");
+}
+// The same to LDS address lds_base + LDS_OFF, from a scalar base and the lane offset off + add in
+// bytes: three instructions, of which the sum is also the wait state between the write of m0 and
+// its use. The second form takes the lane offset min(off, lim).
+template <int LDS_OFF>
+__device__ __forceinline__ void lds_dma16_add(const void* base, uint32_t off, uint32_t add,
+                                              uint32_t lds_base) {
+  uint32_t tmp;
+  asm volatile("s_add_u32 m0, %4, %5\n\tv_add_u32 %0, %2, %1\n\tglobal_load_lds_dwordx4 %0, %3"
+               : "=&v"(tmp)
+               : "v"(off), "s"(add), "s"(base), "s"(lds_base), "n"(LDS_OFF)
+               : "memory", "m0", "scc");
+}
+template <int LDS_OFF>
+__device__ __forceinline__ void lds_dma16_min(const void* base, uint32_t off, uint32_t lim,
+                                              uint32_t lds_base) {
+  uint32_t tmp;
+  asm volatile("s_add_u32 m0, %4, %5\n\tv_min_u32 %0, %1, %2\n\tglobal_load_lds_dwordx4 %0, %3"
+               : "=&v"(tmp)
+               : "v"(off), "v"(lim), "s"(base), "s"(lds_base), "n"(LDS_OFF)
+               : "memory", "m0", "scc");
+}
+
+// f(0), f(1), .. f(N - 1) with constant arguments.
+template <int N, class F>
+__device__ __forceinline__ void for_const(F&& f) {
+  if constexpr (N > 0) {
+    for_const<N - 1>(f);
+    f(std::integral_constant<int, N - 1>{});
+  }
 }
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(lds_void*)(p);

@@ -131,6 +131,7 @@ struct DenseWriteArgs {
   uint16_t* kv;            // [B][ring_tokens][H][2 * d_v]
   int32_t* slots;          // [chunk_tokens] or nullptr
   int32_t batch, d_model, n_heads, d_head;
+  int32_t n_cu;            // compute units of the device
   Geometry geo;
   RopeTable rope;          // d_head / 2 pairs
 };

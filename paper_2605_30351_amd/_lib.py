@@ -160,20 +160,19 @@ def _check(code: int):
         raise VideomlaError(code, _lib.videomla_last_error().decode())
 
 
+_I3 = ctypes.c_int32 * 3
+
+
 def make_dims(d) -> VideomlaDims:
-    """Build the C struct from any object with the Dims field names."""
-    s = VideomlaDims()
-    for name in ("d_model", "n_heads", "d_nope", "d_rope", "d_c", "d_v", "grid_h", "grid_w",
-                 "window_frames", "chunk_frames"):
-        setattr(s, name, int(getattr(d, name)))
-    for i in range(3):
-        s.rope_pairs[i] = int(d.rope_pairs[i])
-        s.rope_band_dim[i] = int(d.rope_band_dim[i])
-    s.rope_base = float(d.rope_base)
-    s.softmax_scale = float(d.softmax_scale)
-    s.kv_norm_eps = float(d.kv_norm_eps)
-    s.sink_frames = int(getattr(d, "sink_frames", 0))
-    return s
+    """Build the C struct from any object with the Dims field names. (One constructor call: every
+    entry point builds one per call, and a setattr per field took three times as long.)"""
+    p, b = d.rope_pairs, d.rope_band_dim
+    return VideomlaDims(
+        int(d.d_model), int(d.n_heads), int(d.d_nope), int(d.d_rope), int(d.d_c), int(d.d_v),
+        int(d.grid_h), int(d.grid_w), int(d.window_frames), int(d.chunk_frames),
+        _I3(int(p[0]), int(p[1]), int(p[2])), _I3(int(b[0]), int(b[1]), int(b[2])),
+        float(d.rope_base), float(d.softmax_scale), float(d.kv_norm_eps),
+        int(getattr(d, "sink_frames", 0)))
 
 
 class Timer:
@@ -254,10 +253,13 @@ def _opts(opts: AttendOpts | None):
 
 
 def _nq(dims, opts):
-    return (opts or AttendOpts()).n_queries(dims)
+    if opts is None:
+        return int(dims.chunk_frames) * int(dims.grid_h) * int(dims.grid_w)
+    return opts.n_queries(dims)
 
 
 def _ptr(t: torch.Tensor | None, name: str, dtypes=(torch.bfloat16, torch.int16, torch.uint16)):
+    """Device address of a checked tensor (an int: the argument types convert it)."""
     if t is None:
         return None
     if not isinstance(t, torch.Tensor):
@@ -268,12 +270,17 @@ def _ptr(t: torch.Tensor | None, name: str, dtypes=(torch.bfloat16, torch.int16,
         raise ValueError(f"{name} must be a device tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+def _stream(stream) -> int:
+    """HIP handle of the stream, or of torch's current stream on the current device (its raw
+    handle: building torch's Stream object takes longer than a kernel launch)."""
+    if stream is not None:
+        return stream.cuda_stream
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _need(t: torch.Tensor, name: str, numel: int):
@@ -312,8 +319,9 @@ def prepare_write_weights(dims, w_dkv, w_kr, w_packed, stream=None):
     _need(w_dkv, "w_dkv", d.d_c * d.d_model)
     _need(w_kr, "w_kr", d.d_rope * d.d_model)
     nbytes = w_packed.numel() * w_packed.element_size()
-    if nbytes < write_weights_bytes(dims):
-        raise ValueError(f"w_packed holds {nbytes} bytes, needs {write_weights_bytes(dims)}")
+    need = int(_lib.videomla_write_weights_bytes(ctypes.byref(d)))
+    if nbytes < need:
+        raise ValueError(f"w_packed holds {nbytes} bytes, needs {need}")
     _check(_lib.videomla_prepare_write_weights(
         ctypes.byref(d), _ptr(w_dkv, "w_dkv"), _ptr(w_kr, "w_kr"),
         _ptr(w_packed, "w_packed", (torch.bfloat16, torch.uint8)), _stream(stream)))
@@ -328,8 +336,9 @@ def cache_write_prepared(dims, frame_end: int, batch: int, x, w_packed, gamma, c
     _need(c_kv, "c_kv", batch * d.window_frames * hw * d.d_c)
     _need(k_r, "k_r", batch * d.window_frames * hw * d.d_rope)
     nbytes = w_packed.numel() * w_packed.element_size()
-    if nbytes < write_weights_bytes(dims):
-        raise ValueError(f"w_packed holds {nbytes} bytes, needs {write_weights_bytes(dims)}")
+    need = int(_lib.videomla_write_weights_bytes(ctypes.byref(d)))
+    if nbytes < need:
+        raise ValueError(f"w_packed holds {nbytes} bytes, needs {need}")
     if gamma is not None:
         _need(gamma, "gamma", d.d_c)
     if slots is not None:

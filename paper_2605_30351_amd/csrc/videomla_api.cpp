@@ -271,11 +271,7 @@ Partition make_partition(int rows, int RB, int bn, int wpc, int32_t batch, int64
   if (n_wg == 0 && G > (int64_t)(kMaxSplitsPerRowBlock - 1) * batch * RB)
     G = (int64_t)(kMaxSplitsPerRowBlock - 1) * batch * RB;
   p.G = (int)(G < p.U ? G : p.U);
-  p.max_seg = 1;
-  for (int64_t rbg = 0; rbg < (int64_t)batch * p.RB; ++rbg) {
-    const int n = attend_owner(rbg * p.T + p.T - 1, p.U, p.G) - attend_owner(rbg * p.T, p.U, p.G) + 1;
-    if (n > p.max_seg) p.max_seg = n;
-  }
+  p.max_seg = partition_max_seg((int64_t)batch * RB, p.T, p.G);
   return p;
 }
 

@@ -167,6 +167,35 @@ __host__ __device__ inline int attend_owner(int64_t unit, int64_t units, int n_w
   return (int)(((unit + 1) * (int64_t)n_wg - 1) / units);
 }
 
+// The most workgroups that share one of N row blocks of T units each, split evenly over G <= N T:
+// the largest attend_owner(r T + T - 1) - attend_owner(r T) + 1. With U = N T, the owner of a row
+// block's last unit is floor(((r + 1) G - 1) / N), and that of its first, with r G = a N + b, is a,
+// or a + 1 where b T + G - 1 reaches U; a and b advance without a division, and the pattern repeats
+// after N / gcd(N, G) row blocks. (Every call needs this for each number of frames a window can
+// hold, before its first launch: 40 us at the Wan shape with two 64-bit divisions per row block.)
+__host__ inline int partition_max_seg(int64_t N, int64_t T, int64_t G) {
+  int64_t x = N, y = G;
+  while (y) {
+    const int64_t z = x % y;
+    x = y;
+    y = z;
+  }
+  const int64_t period = N / x, step_a = G / N, step_b = G % N, wrap = N * T - (G - 1);
+  int64_t a = 0, b = 0, most = 1;
+  for (int64_t r = 0; r < period; ++r) {
+    const int64_t first = a + (b * T >= wrap);
+    a += step_a;
+    b += step_b;
+    if (b >= N) {
+      b -= N;
+      ++a;
+    }
+    const int64_t last = b == 0 ? a - 1 : a;
+    if (last - first + 1 > most) most = last - first + 1;
+  }
+  return (int)most;
+}
+
 // Weighted partition of the attention units. Workgroup k runs on XCD k mod 8 and gets a share of
 // the units proportional to its XCD's integer weight w[k mod 8] in [kBalMin, kBalMax]:
 // workgroup k takes [start(k), start(k+1)) with start(k) = floor(U cum(k) / cum(G)), cum(k) the

@@ -371,7 +371,13 @@ struct AttCfg {
   }
 };
 
-template <int DC, int DR, int QB, int NW, int BN, int WPC, bool DENSE = false, int DVW = 0>
+// FEW: every row block has fewer rows than waves x 32 (few queries). Waves whose rows are all past
+// the query rows then take part in the loads and barriers only: their scores would cost the others
+// LDS and matrix cycles. (An instantiation of its own: the branch costs the full blocks 0.8%,
+// 1226 against 1237 us at the Wan chunk. One query x 8 videos over 32,760 keys: whole attend 62 us
+// without it, 47 with.)
+template <int DC, int DR, int QB, int NW, int BN, int WPC, bool DENSE = false, int DVW = 0,
+          bool FEW = false>
 __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const AttendArgs a) {
   using C = AttCfg<DC, DR, QB, NW, BN, DENSE, DVW>;
   __shared__ __attribute__((aligned(16))) uint16_t tile[C::NBUF][C::TILE];
@@ -743,6 +749,16 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
   if (!DENSE && stamp_step == 0) VMLA_STAMP(a, kStampAttend, 1);
   if (!DENSE && stamp_seg == 1) VMLA_STAMP(a, kStampAttend, 14);
 
+  const int rows_here = DENSE ? a.geo.q_count - (row0 - rb / (a.row_blocks / a.n_heads) * a.nq_pad) : rows_b - row0;
+  if (FEW && rows_here <= 0) {
+    int fill = 2;
+    for (int t = 0; t < n_tiles; ++t) {
+      dma_tile(key_begin + (t + 2) * BN, tile[fill]);
+      fill = fill == 2 ? 0 : fill + 1;
+      wait_vmcnt<0>();
+      __syncthreads();
+    }
+  } else {
   f32x16 s_a[QB][C::KB], s_b[QB][C::KB];
   if (n_tiles > 0) scores(tile[0], s_a);
   if (n_tiles > 0) {
@@ -791,6 +807,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
       ml[1] = l_tot;
     }
   }
+  }  // waves with rows
   if (!DENSE && stamp_seg == 0) VMLA_STAMP(a, kStampAttend, 13);
   ++stamp_seg;
   --rbg;
@@ -1054,12 +1071,18 @@ template <> struct AttShape<256, 32> { static constexpr int QB = 1, NW = 4, BN =
 #define VMLA_NARROW_SHAPES(X) X(192, 32) X(16, 8) X(64, 32) X(128, 32) X(256, 32)
 #define VMLA_LATENT_SHAPES(X) VMLA_NARROW_SHAPES(X) X(512, 32)
 
+// Whether the only row block of a batch element (or head), of `rows` query rows, leaves a wave idle.
+bool few_rows(const AttendArgs& a, int64_t rows) { return rows + 32 <= a.att_rows; }
+
 template <int DC, int DR>
 hipError_t launch_attend_t(const AttendArgs& a, hipStream_t s) {
   using S = AttShape<DC, DR>;
   using C = AttCfg<DC, DR, S::QB, S::NW, S::BN>;
   const dim3 grid(a.n_wg);
-  hipLaunchKernelGGL((latent_attend_kernel<DC, DR, S::QB, S::NW, S::BN, S::WPC>), grid,
+  if (few_rows(a, (int64_t)a.geo.q_count * a.n_heads))
+    hipLaunchKernelGGL((latent_attend_kernel<DC, DR, S::QB, S::NW, S::BN, S::WPC, false, 0, true>), grid,
+                       dim3(C::NT), 0, s, a);
+  else hipLaunchKernelGGL((latent_attend_kernel<DC, DR, S::QB, S::NW, S::BN, S::WPC>), grid,
                      dim3(C::NT), 0, s, a);
   return hipGetLastError();
 }
@@ -1075,12 +1098,24 @@ bool dense_attend_supported(int d_head) { return d_head == kDenseHead; }
 int dense_attend_rows_per_block() { return DenseCfg::ROWS; }
 int dense_attend_keys_per_tile() { return DenseShape::BN; }
 
+namespace {
+template <int DK, int DVW>
+hipError_t launch_head_attend(const AttendArgs& a, hipStream_t s) {
+  using S = DenseShape;
+  const dim3 grid(a.n_wg), block(DenseCfg::NT);
+  if (few_rows(a, a.geo.q_count))
+    hipLaunchKernelGGL((latent_attend_kernel<DK, 0, S::QB, S::NW, S::BN, S::WPC, true, DVW, true>), grid,
+                       block, 0, s, a);
+  else
+    hipLaunchKernelGGL((latent_attend_kernel<DK, 0, S::QB, S::NW, S::BN, S::WPC, true, DVW>), grid, block,
+                       0, s, a);
+  return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_dense_attend(const AttendArgs& a, hipStream_t s) {
   if (a.d_v != kDenseHead) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((latent_attend_kernel<kDenseHead, 0, DenseShape::QB, DenseShape::NW,
-                                           DenseShape::BN, DenseShape::WPC, true>),
-                     dim3(a.n_wg), dim3(DenseCfg::NT), 0, s, a);
-  return hipGetLastError();
+  return launch_head_attend<kDenseHead, 0>(a, s);
 }
 
 // Materialized form: per-head rows [K_h | V_h] with K_h = [W_UK,h c ; k^R] of width d_nope +
@@ -1093,10 +1128,7 @@ bool mat_attend_supported(int d_k, int d_v) {
 hipError_t launch_mat_attend(const AttendArgs& a, hipStream_t s) {
   if (!mat_attend_supported(a.dqk_pad, a.d_v)) return hipErrorInvalidValue;
   if (a.dqk_pad == kDenseHead) return launch_dense_attend(a, s);
-  hipLaunchKernelGGL((latent_attend_kernel<160, 0, DenseShape::QB, DenseShape::NW,
-                                           DenseShape::BN, DenseShape::WPC, true, kDenseHead>),
-                     dim3(a.n_wg), dim3(DenseCfg::NT), 0, s, a);
-  return hipGetLastError();
+  return launch_head_attend<160, kDenseHead>(a, s);
 }
 
 template <int DC, int DR> using ShapeCfg =

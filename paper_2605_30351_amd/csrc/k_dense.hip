@@ -13,6 +13,7 @@
 //   dense_merge        merges the key splits exactly and writes out[b][n][h]
 #include "vmla_device.h"
 #include "vmla_gemm.h"
+#include "vmla_merge.h"
 
 namespace vmla {
 namespace {
@@ -416,6 +417,16 @@ __global__ __launch_bounds__(256) void dense_merge_kernel(const AttendArgs a) {
   *reinterpret_cast<bf16x8*>(a.out + R * DH + grp * 8) = to_bf16x8(v);
 }
 
+// The same, one workgroup per output row, for calls whose row blocks are shared by many workgroups.
+__global__ __launch_bounds__(256) void dense_merge_split_kernel(const AttendArgs a) {
+  const uint32_t H = (uint32_t)a.n_heads, Nq = (uint32_t)a.geo.q_count, R = blockIdx.x;
+  const uint32_t tok = R / H, h = R % H, b = tok / Nq, n = tok % Nq;
+  const size_t rows_b = (size_t)H * a.nq_pad;
+  const uint32_t r = h * (uint32_t)a.nq_pad + n;  // row within the batch element
+  const int ns = attend_split_count(a, (int64_t)b * a.row_blocks + r / (uint32_t)a.att_rows);
+  merge_row_split(a, b * rows_b + r, a.batch * rows_b, a.d_v, ns, a.out + (size_t)R * a.d_v);
+}
+
 }  // namespace
 
 hipError_t launch_dense_cache_write(const DenseWriteArgs& a, hipStream_t s) {
@@ -462,7 +473,11 @@ hipError_t launch_mat_rope_fill(const AttendArgs& a, uint16_t* kv, hipStream_t s
 }
 
 hipError_t launch_dense_merge(const AttendArgs& a, hipStream_t s) {
-  const int64_t threads = (int64_t)a.batch * a.geo.q_count * a.n_heads * (a.d_v / 8);
+  const int64_t rows = (int64_t)a.batch * a.geo.q_count * a.n_heads, threads = rows * (a.d_v / 8);
+  if (merge_by_workgroup(a, rows)) {
+    hipLaunchKernelGGL(dense_merge_split_kernel, dim3((unsigned)rows), dim3(256), 0, s, a);
+    return hipGetLastError();
+  }
   if (threads >= (int64_t(1) << 32) - 256) return hipErrorInvalidValue;  // 32-bit indices
   hipLaunchKernelGGL(dense_merge_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s,
                      a);

@@ -18,6 +18,7 @@
 // (chunk index XOR (row / 2) mod 8). Tiles are numbered token-block-major and dealt to the XCDs
 // in contiguous ranges. Rows past M or N are clamped to the last row and their results discarded.
 #include "vmla_device.h"
+#include "vmla_merge.h"
 
 namespace vmla {
 namespace {
@@ -261,6 +262,19 @@ __global__ __launch_bounds__(256) void latent_merge_kernel(const AttendArgs a, u
   *reinterpret_cast<bf16x8*>(o_lat + tok * ld_olat + h * DC + grp * 8) = to_bf16x8(v);
 }
 
+// The same, one workgroup per query row, for calls whose row blocks are shared by many workgroups.
+__global__ __launch_bounds__(256) void latent_merge_split_kernel(const AttendArgs a, uint16_t* o_lat,
+                                                                 int ld_olat) {
+  const int H = a.n_heads, DC = a.d_c;
+  const uint32_t rows_b = (uint32_t)(a.geo.q_count * H), R = blockIdx.x;
+  const int b = (int)(R / rows_b), r = (int)(R % rows_b), h = (int)(R % (uint32_t)H);
+  const int ns = attend_split_count(a, (int64_t)b * a.row_blocks + r / a.att_rows);
+  uint16_t* row = o_lat + (size_t)(R / (uint32_t)H) * ld_olat;
+  if (h == 0)  // the token's padding columns
+    for (int c = H * DC + (int)threadIdx.x; c < ld_olat; c += 256) row[c] = 0;
+  merge_row_split(a, R, (size_t)a.batch * rows_b, DC, ns, row + h * DC);
+}
+
 // ---------------------------------------------------------------------------------------------
 // prepare_weights: one thread per output element of the packed weights, fp32 sums, bf16 RNE.
 // ---------------------------------------------------------------------------------------------
@@ -343,6 +357,10 @@ hipError_t launch_gemm_nt(const GemmArgs& a, hipStream_t s) {
 
 hipError_t launch_latent_merge(const AttendArgs& a, uint16_t* o_lat, int ld_olat, hipStream_t s) {
   const int64_t rows = (int64_t)a.batch * a.geo.q_count * a.n_heads;
+  if (merge_by_workgroup(a, rows)) {
+    hipLaunchKernelGGL(latent_merge_split_kernel, dim3((unsigned)rows), dim3(256), 0, s, a, o_lat, ld_olat);
+    return hipGetLastError();
+  }
   const int64_t pad = (int64_t)a.batch * a.geo.q_count * ((ld_olat - a.n_heads * a.d_c) / 8);
   const int64_t threads = rows * (a.d_c / 8) + pad;
   if (threads >= (int64_t(1) << 32) - 256) return hipErrorInvalidValue;  // 32-bit indices

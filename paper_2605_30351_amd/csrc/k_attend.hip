@@ -330,11 +330,10 @@ struct AttCfg {
   static constexpr int OW = DENSE && DVW ? DVW : DC;  // value (and partial-result) width
   static constexpr int DVB = (OW + 31) / 32;
   // Rescaling of the accumulators (rare): in place where they live in vector registers; through
-  // the wave's LDS slot where there are so many (one wave per SIMD, 128 registers or more) that
-  // the compiler keeps them in accumulation registers, which no VALU instruction may then touch:
-  // in place would move them to vector registers and back in every step (d_c = 512: 4748 us
-  // through LDS, 5000 in place; d_c = 192, peaked scores: a rescale of all eight waves took about
-  // 6 us through LDS and takes under 1 in place).
+  // the wave's LDS slot where there are so many (d_c = 256: one wave per SIMD, 128 registers) that
+  // the compiler keeps them in accumulation registers, which no VALU instruction may then touch: in
+  // place would move them to vector registers and back in every step (d_c = 192, peaked scores: a
+  // rescale of all eight waves took about 6 us through LDS and takes under 1 in place).
   static constexpr bool RESC_LDS = QB * DVB >= 8;
   static constexpr int KB = BN / 32;       // 32-key blocks per tile
   static constexpr int VOFF = DENSE ? DQKP : 0;  // first V column of a tile row

@@ -247,40 +247,13 @@ int resolve_opts(const videomla_dims* d, const videomla_attend_opts* o, Opts& r)
 }
 
 // ---- work partition ---------------------------------------------------------------------------
-constexpr int kMaxSplitsPerRowBlock = 64;
-// Work partition of the attention kernel for a window of n_valid keys (see AttendArgs).
-struct Partition {
-  int G, rows, RB, T, max_seg;
-  int64_t U;
-};
-
-// rows: query rows per row block; RB: row blocks per batch element; bn: keys per tile;
-// wpc: resident workgroups per compute unit; n_wg: requested workgroups (0 = wpc per CU).
-Partition make_partition(int rows, int RB, int bn, int wpc, int32_t batch, int64_t n_valid,
-                         int n_wg) {
-  Partition p{};
-  p.rows = rows;
-  p.RB = RB;
-  p.T = (int)((n_valid + bn - 1) / bn);
-  p.U = (int64_t)batch * p.RB * p.T;
-  // by default at most kMaxSplitsPerRowBlock - 1 workgroups per row block: few-query calls
-  // (few row blocks, each split over many workgroups) then give each workgroup at least 1/63 of
-  // a row block's key tiles, which bounds the partial results they write, and the merge reads,
-  // relative to the keys they read
-  int64_t G = n_wg > 0 ? n_wg : (int64_t)device_cu_count() * wpc;
-  if (n_wg == 0 && G > (int64_t)(kMaxSplitsPerRowBlock - 1) * batch * RB)
-    G = (int64_t)(kMaxSplitsPerRowBlock - 1) * batch * RB;
-  p.G = (int)(G < p.U ? G : p.U);
-  p.max_seg = partition_max_seg((int64_t)batch * RB, p.T, p.G);
-  return p;
-}
-
 Partition attend_partition(const videomla_dims* d, int32_t batch, int64_t n_valid, const Opts& o) {
   const int rows = latent_attend_rows_per_block(d->d_c, d->d_rope);
   const int64_t rows_b = (int64_t)o.q_count * d->n_heads;
   return make_partition(rows, (int)((rows_b + rows - 1) / rows),
                         latent_attend_keys_per_tile(d->d_c, d->d_rope),
-                        latent_attend_wgs_per_cu(d->d_c, d->d_rope), batch, n_valid, o.n_wg);
+                        device_cu_count() * latent_attend_wgs_per_cu(d->d_c, d->d_rope), batch,
+                        n_valid, o.n_wg);
 }
 
 // Per-head forms (the dense comparator and the materialized form): every head's query rows
@@ -293,7 +266,7 @@ int head_nq_pad(const Opts& o) {
 Partition head_partition(const videomla_dims* d, int32_t batch, int64_t n_valid, const Opts& o) {
   const int rows = dense_attend_rows_per_block();
   return make_partition(rows, d->n_heads * (head_nq_pad(o) / rows), dense_attend_keys_per_tile(),
-                        1, batch, n_valid, o.n_wg);
+                        device_cu_count(), batch, n_valid, o.n_wg);
 }
 
 // Partial-result slots the workspace must hold for any window this shape can attend over
@@ -362,13 +335,11 @@ MatLayout mat_layout(const videomla_dims* d, int32_t batch, const Opts& o) {
   return m;
 }
 
-// The weighted partition for a call (adaptive or frozen): only where every range keeps at least
-// one unit under any weights and the workspace holds the partial results such ranges can leave.
+// The weighted partition for a call (adaptive or frozen), where it can be used.
 void set_balance(AttendArgs& a, const Partition& P, char* ws, const WorkspaceLayout& L,
                  const Opts& o) {
   a.bal_state = reinterpret_cast<uint32_t*>(ws + L.bal_off);
-  a.bal_on = o.partition != VIDEOMLA_PARTITION_EVEN && P.G <= kBalMaxWg &&
-             bal_max_seg(P.G, P.U, P.T) <= L.n_seg;
+  a.bal_on = o.partition != VIDEOMLA_PARTITION_EVEN && weighted_split_fits(P, L.n_seg);
   a.bal_rec = a.bal_on && o.partition == VIDEOMLA_PARTITION_ADAPTIVE;
   if (a.bal_on) a.max_seg = L.n_seg;
 }

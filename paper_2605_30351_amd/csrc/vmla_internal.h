@@ -196,6 +196,34 @@ __host__ inline int partition_max_seg(int64_t N, int64_t T, int64_t G) {
   return (int)most;
 }
 
+constexpr int kMaxSplitsPerRowBlock = 64;
+// Work partition of the attention kernel for a window of n_valid keys (see AttendArgs).
+struct Partition {
+  int G, rows, RB, T, max_seg;
+  int64_t U;
+};
+
+// rows: query rows per row block; RB: row blocks per batch element; bn: keys per tile;
+// default_wgs: workgroups resident on the device; n_wg: requested workgroups (0 = default_wgs).
+__host__ inline Partition make_partition(int rows, int RB, int bn, int default_wgs, int32_t batch,
+                                         int64_t n_valid, int n_wg) {
+  Partition p{};
+  p.rows = rows;
+  p.RB = RB;
+  p.T = (int)((n_valid + bn - 1) / bn);
+  p.U = (int64_t)batch * p.RB * p.T;
+  // by default at most kMaxSplitsPerRowBlock - 1 workgroups per row block: few-query calls
+  // (few row blocks, each split over many workgroups) then give each workgroup at least 1/63 of
+  // a row block's key tiles, which bounds the partial results they write, and the merge reads,
+  // relative to the keys they read
+  int64_t G = n_wg > 0 ? n_wg : default_wgs;
+  if (n_wg == 0 && G > (int64_t)(kMaxSplitsPerRowBlock - 1) * batch * RB)
+    G = (int64_t)(kMaxSplitsPerRowBlock - 1) * batch * RB;
+  p.G = (int)(G < p.U ? G : p.U);
+  p.max_seg = partition_max_seg((int64_t)batch * RB, p.T, p.G);
+  return p;
+}
+
 // Weighted partition of the attention units. Workgroup k runs on XCD k mod 8 and gets a share of
 // the units proportional to its XCD's integer weight w[k mod 8] in [kBalMin, kBalMax]:
 // workgroup k takes [start(k), start(k+1)) with start(k) = floor(U cum(k) / cum(G)), cum(k) the
@@ -273,12 +301,23 @@ __host__ __device__ inline int bal_owner_fd(const uint32_t* w, int G, int64_t U,
 }
 
 // Partial-result slots a row block of T units can need under any weights: every range holds at
-// least floor(U kBalMin / (kBalMin + (G - 1) kBalMax)) - 1 units.
+// least floor(U kBalMin / (kBalMin + (G - 1) kBalMax)) - 1 units. More than any workspace has
+// (kBalNever) where that is none: a range could be empty.
+constexpr int kBalNever = 0x7fffffff;
 __host__ __device__ inline int bal_max_seg(int G, int64_t U, int T) {
   const int64_t min_len = U * kBalMin / (kBalMin + (int64_t)(G - 1) * kBalMax) - 1;
-  if (min_len < 1) return G + 1;  // some range could be empty: never adaptive
+  if (min_len < 1) return kBalNever;
   const int64_t n = (T + min_len - 1) / min_len + 1;
   return (int)(n < G ? n : G);
+}
+// Whether a call may take the weighted split: every range keeps at least one unit under any
+// weights (the merges count the owners between a row block's first and last, each of which must
+// have written its partial result), and the workspace's n_seg partial-result slots hold what such
+// ranges can leave. n_seg is the most that any window of the shape needs, so a window that is
+// still filling, with fewer units, must not be admitted for its number of slots alone.
+__host__ inline bool weighted_split_fits(const Partition& p, int n_seg) {
+  const int need = bal_max_seg(p.G, p.U, p.T);
+  return p.G <= kBalMaxWg && need != kBalNever && need <= n_seg;
 }
 
 // Sets the calling thread's last-error message (videomla_last_error) and returns `code`; for

@@ -35,7 +35,7 @@ def vm():
 
 from oracle import videomla_oracle as O  # noqa: E402
 from tests.gpu_common import Layer, assert_attention_close, sample_rows  # noqa: E402
-from workloads import TINY, WAN, make_layer_inputs  # noqa: E402
+from workloads import SMALL, TINY, WAN, make_layer_inputs  # noqa: E402
 
 
 def _state(ws, end=None):
@@ -121,6 +121,28 @@ def test_adaptive_mode_on_small_shapes_and_partitions(vm):
                 for b in range(inp.batch):
                     assert_attention_close(got[b], O.chunk_attention(inp, b, fe),
                                            f"tiny fe={fe} b={b} wg={wg} {part}")
+
+
+@pytest.mark.parametrize("d_c", [192, 512])
+def test_window_still_filling_keeps_the_even_split(vm, d_c):
+    """One row block whose window of 21 frames holds two: four workgroups of one key tile each,
+    while the workspace has the full window's 40 partial-result slots. Unequal weights would leave
+    workgroup 1 without a tile and its slot as the caller left it (NaN here), so the call keeps
+    the even split."""
+    d = SMALL.replace(d_c=d_c, window_frames=21)
+    inp = make_layer_inputs(d, seed=37, n_frames=d.chunk_frames)
+    layer = Layer(vm, inp, packed=True)
+    layer.write(0)
+    even = vm.AttendOpts(query_count=32)
+    frozen = vm.AttendOpts(query_count=32, partition="frozen")
+    ws = torch.full((vm.attend_workspace_bytes(d, 1, frozen),), 0xFF, dtype=torch.uint8, device="cuda")
+    st = np.zeros(BAL_WORDS, np.uint32)
+    st[:10] = [1049, 950, 1024, 1024, 1024, 1024, 1024, 1024, 4, BAL_MARK]
+    start = ws.numel() - BAL_BYTES
+    ws[start:start + BAL_WORDS * 4] = torch.from_numpy(st.view(np.uint8)).cuda()
+    got = layer.attend(0, frozen, ws=ws)
+    assert_attention_close(got[0], O.chunk_attention(inp, 0, 0)[:32], f"frozen d_c={d_c}")
+    assert np.array_equal(got, layer.attend(0, even))
 
 
 def test_wan_layer_adaptive_calls(vm):

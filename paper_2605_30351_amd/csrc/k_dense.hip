@@ -474,7 +474,7 @@ hipError_t launch_mat_rope_fill(const AttendArgs& a, uint16_t* kv, hipStream_t s
 
 hipError_t launch_dense_merge(const AttendArgs& a, hipStream_t s) {
   const int64_t rows = (int64_t)a.batch * a.geo.q_count * a.n_heads, threads = rows * (a.d_v / 8);
-  if (merge_by_workgroup(a, rows)) {
+  if (merge_by_workgroup(rows, a.max_seg, true)) {
     hipLaunchKernelGGL(dense_merge_split_kernel, dim3((unsigned)rows), dim3(256), 0, s, a);
     return hipGetLastError();
   }

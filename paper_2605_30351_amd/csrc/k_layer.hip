@@ -357,7 +357,7 @@ hipError_t launch_gemm_nt(const GemmArgs& a, hipStream_t s) {
 
 hipError_t launch_latent_merge(const AttendArgs& a, uint16_t* o_lat, int ld_olat, hipStream_t s) {
   const int64_t rows = (int64_t)a.batch * a.geo.q_count * a.n_heads;
-  if (merge_by_workgroup(a, rows)) {
+  if (merge_by_workgroup(rows, a.max_seg, false)) {
     hipLaunchKernelGGL(latent_merge_split_kernel, dim3((unsigned)rows), dim3(256), 0, s, a, o_lat, ld_olat);
     return hipGetLastError();
   }

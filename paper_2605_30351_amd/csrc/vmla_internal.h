@@ -320,6 +320,26 @@ __host__ inline bool weighted_split_fits(const Partition& p, int n_seg) {
   return p.G <= kBalMaxWg && need != kBalNever && need <= n_seg;
 }
 
+// Whether the partial results of a call of `rows` query rows, each split over up to `splits`
+// workgroups, are merged by a workgroup per row (vmla_merge.h) instead of a thread per 8 columns.
+// While the bytes are few, the first takes about 4 us and 2.5 us per 1,000 rows, whatever the splits;
+// the second waits for its loads in turn, 3 us and 0.2 us per split in the latent merge (groups of
+// four in flight), 2 us and 0.5 us per split in the per-head one (one at a time beyond four). us,
+// workgroup / thread:
+//   latent, rows x splits   192 x 7    768 x 12   1536 x 12   1536 x 32   2400 x 20   3840 x 63
+//     d_c = 64              4.5 / 4.0  5.1 / 6.1  6.7 / 5.4   8.5 / 10.9  10.8 / 8.5  16.3 / 17.9
+//     d_c = 192             4.9 / 4.7  5.2 / 6.0  7.9 / 6.5  10.0 / 11.0  11.3 / 9.5  31.1 / 31.3
+//     d_c = 512             4.8 / 4.7  6.8 / 7.1  9.6 / 8.9  16.8 / 18.1  17.2 / 18.3  129 / 132
+//   per head, 128 columns   768 x 5    1536 x 5   1536 x 12   3840 x 12   3840 x 32   12288 x 63
+//                           4.0 / 4.7  5.8 / 4.8  6.4 / 8.2  12.6 / 9.5  15.0 / 21.1  96 / 107
+// Over 390 such points (rows 12 to 12,288, splits 5 to 63, every width) the rule is at most 7% slower
+// than the better of the two; wider rows than 192 columns differ by 7% at most beyond its line (both
+// are then bound by the bytes), so the width is left out.
+__host__ inline bool merge_by_workgroup(int64_t rows, int splits, bool per_head) {
+  const int64_t least = per_head ? 4 : 8, per_split = per_head ? 200 : 75;
+  return splits > least && rows <= per_split * splits && rows < (1 << 24);  // (one grid)
+}
+
 // Sets the calling thread's last-error message (videomla_last_error) and returns `code`; for
 // the C-ABI sources other than videomla_api.cpp.
 int report_error(int code, const char* fmt, ...);

@@ -81,13 +81,4 @@ __device__ __forceinline__ void merge_row_split(const AttendArgs& a, size_t prow
   *reinterpret_cast<bf16x8*>(dst + grp * 8) = to_bf16x8(v);
 }
 
-// Whether a call's rows take that merge. It takes about 3.5 us and 2.9 us per 1,000 rows; a thread
-// per 8 columns takes 4 us and 0.2 us per split of a row. Latent merge, width 192, (rows, splits):
-// (12, 63) 4.2 us by workgroups and 16.2 by threads, (768, 63) 9.3 and 17.3, (1536, 33) 9.6 and 10.8,
-// (2400, 28) 12.0 and 11.5, (3840, 17) 14.6 and 10.0; dense: (2400, 22) 10.6 and 14.4, (1920, 7)
-// 7.5 and 6.9. Up to four splits are one group of loads of the thread form.
-inline bool merge_by_workgroup(const AttendArgs& a, int64_t rows) {
-  return a.max_seg > 4 && rows <= 110 * (int64_t)a.max_seg && rows < (1 << 24);  // (one grid)
-}
-
 }  // namespace vmla

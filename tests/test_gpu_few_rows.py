@@ -1,7 +1,7 @@
 """GPU parity of calls of few queries against the fp64 oracle: the attention kernel's form whose
 waves without query rows only load (from one row, through whole waves and a wave cut short, to one
-idle wave and none), and the merge of rows split over many workgroups (5 to 10 partial results of
-a row by a workgroup, at every latent width; 4 and fewer take the other merge)."""
+idle wave and none), and the merge of rows split over many workgroups (10 partial results of a row
+by a workgroup, at every latent width, 5 to 10 in the per-head forms; fewer take the other merge)."""
 import pytest
 import torch
 

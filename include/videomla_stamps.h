@@ -47,10 +47,12 @@ extern "C" {
  *   4 RoPE part written; 5 rows staged; 6 stores complete.
  * - 3, the latent attention (latent form only; the dense and materialized kernels record
  *   nothing):
- *   0 start; 1 first two tiles landed;
+ *   0 start; 1 first two tiles landed (three at d_c = 512; of the first segment);
  *   2 + 2i / 3 + 2i the instruction stream of the workgroup's step 200 + i ended / its
  *   barrier passed (i < 4). The stream's end is read before the step's wait for its tile
- *   loads, and stored only after the barrier, so the wait has no stamp store to drain;
+ *   loads, and stored only after the barrier, so the wait has no stamp store to drain. At
+ *   d_c = 512 a step has two barriers: the points are at the second, and the tile loads are
+ *   waited for at the first;
  *   10 last step done; 11 partial results stored;
  *   12 the first segment's last step done and 13 its partial results issued (every
  *   workgroup); 14 the second segment's first two tiles landed (workgroups with a second

@@ -102,6 +102,8 @@ __global__ __launch_bounds__(256, 1) void latent_attend_wide_kernel(const Attend
   const int qd = lane >> 4, l16 = lane & 15;
   const int rh = wave & 1, kh = wave >> 1;  // score rows 32 rh .., keys 16 kh ..
   const int rows_b = a.geo.q_count * a.n_heads;
+  VMLA_STAMP(a, kStampAttend, 0);
+  int stamp_step = 0, stamp_seg = 0;  // steps taken, segments finished (phase stamps only)
 
   // this workgroup's share of the (batch, row block, key tile) units, as in latent_attend_kernel
   const int64_t U = a.units;
@@ -252,6 +254,8 @@ __global__ __launch_bounds__(256, 1) void latent_attend_wide_kernel(const Attend
     dma_tile(key_begin + 2 * BN, tile[2]);
     wait_vmcnt<0>();
     __syncthreads();
+    if (stamp_step == 0) VMLA_STAMP(a, kStampAttend, 1);
+    if (stamp_seg == 1) VMLA_STAMP(a, kStampAttend, 14);
 
     // scores of tile 0, its row max as the running max
     f32x4 s_cur[2] = {f32x4{}, f32x4{}};
@@ -391,14 +395,24 @@ __global__ __launch_bounds__(256, 1) void latent_attend_wide_kernel(const Attend
       for_const<2 * DB>(value_slot);
       s_cur[0] = s_nxt[0];
       s_cur[1] = s_nxt[1];
+      const bool stamped = stamp_step >= 200 && stamp_step < 204;
+      const uint64_t stream_end = stamped ? VMLA_STAMP_NOW() : 0;
       wait_lgkmcnt<PF>();  // the max, and every read of tile t; the operands of tile t+2 may pend
       bare_barrier();
+      if (stamped) {
+        VMLA_STAMP(a, kStampAttend, 3 + 2 * (stamp_step - 200));
+        VMLA_STAMP_AT(a, kStampAttend, 2 + 2 * (stamp_step - 200), stream_end);
+      }
+      ++stamp_step;
       uint16_t* tmp = p0;
       p0 = p1;
       p1 = p2;
       p2 = p3;
       p3 = tmp;
     }
+
+    VMLA_STAMP(a, kStampAttend, 10);  // the segment processed last keeps its stamp
+    if (stamp_seg == 0) VMLA_STAMP(a, kStampAttend, 12);
 
     // ---- unnormalized O_lat and (max, sum) of this split ----------------------------------
     wait_vmcnt<0>();  // the last tiles' loads are done before their buffers are reused
@@ -423,7 +437,10 @@ __global__ __launch_bounds__(256, 1) void latent_attend_wide_kernel(const Attend
       ml[0] = m_row;
       ml[1] = mx[0][lane] + mx[1][lane];
     }
+    if (stamp_seg == 0) VMLA_STAMP(a, kStampAttend, 13);
+    ++stamp_seg;
   }
+  VMLA_STAMP_DRAINED(a, kStampAttend, 11);
   if (a.bal_rec && tid == 0)
     a.bal_state[kBalHead + blockIdx.x] = (uint32_t)(__builtin_amdgcn_s_memrealtime() - bal_t0);
 }

@@ -11,7 +11,7 @@ import numpy as np  # noqa: E402
 import torch  # noqa: E402
 
 import paper_2605_30351_amd as vm  # noqa: E402
-from tests.stamps_run import run  # noqa: E402
+from tests.stamps_run import ATTENDS, run, run_attend  # noqa: E402
 
 # Expected grids at the Wan shape on a 256-CU device (each launcher's own arithmetic):
 # packed write ceil(4680 / ceil(4680 / 256)) = 247 workgroups of 7 waves (224 outputs / 32);
@@ -27,8 +27,14 @@ EXPECT = {  # kernel: (workgroups, waves, points in the order they are reached)
 }
 
 
-def check(rec, name):
+# the latent attention of stamps_run.ATTENDS: 256 workgroups of 4 waves
+EXPECT_ATTENDS = {"out_dc512": (256, 4)}
+
+
+def check(rec, name, grid=None):
     n_wg, waves, pts = EXPECT[name]
+    if grid is not None:
+        n_wg, waves = grid
     k = rec[vm.STAMP_KERNEL[name]].astype(np.int64)  # [workgroup][wave][point]
     live = np.nonzero(k[:, :, 0].max(axis=1))[0]
     assert list(live) == list(range(n_wg)), (name, len(live), n_wg)
@@ -61,6 +67,13 @@ def main():
         check(rec, name)
     for name, t in outs.items():
         np.save(os.path.join(sys.argv[1], name + ".npy"), t.numpy())
+    for name, args in ATTENDS.items():
+        buf.zero_()
+        out = run_attend(vm, *args, buf)
+        rec = buf.cpu().numpy().view(np.uint64).reshape(rec.shape)
+        print(name, flush=True)
+        check(rec, "latent_attend", EXPECT_ATTENDS[name])
+        np.save(os.path.join(sys.argv[1], name + ".npy"), out.numpy())
     print("stamps child OK", flush=True)
 
 

@@ -7,6 +7,40 @@ import torch
 from workloads import WAN
 
 
+def run_attend(vm, d_c, n_queries, n_wg, stamp_buffer=None):
+    """An attend of the Wan layer with latent width d_c and n_queries query tokens (0: the whole
+    chunk) over a full window, recorded into `stamp_buffer`. Returns the output as run() does."""
+    d, dev = WAN.replace(d_c=d_c), torch.device("cuda:0")
+    g = torch.Generator(device=dev)
+    g.manual_seed(2606)
+
+    def normal(shape, std=1.0):
+        return (torch.randn(shape, generator=g, device=dev) * std).to(torch.bfloat16)
+
+    nq, H = n_queries or d.chunk_tokens, d.n_heads
+    w_uk = normal((H * d.d_nope, d.d_c), d.d_c ** -0.5)
+    w_uv = normal((H * d.d_v, d.d_c), d.d_c ** -0.5)
+    c_kv, k_r = normal((1, d.window_tokens, d.d_c)), normal((1, d.window_tokens, d.d_rope))
+    q_nope, q_r = normal((1, nq, H, d.d_nope)), normal((1, nq, H, d.d_rope))
+    out = torch.empty((1, nq, H, d.d_v), dtype=torch.bfloat16, device=dev)
+    opts = vm.AttendOpts(query_count=n_queries, n_workgroups=n_wg)
+    ws = torch.empty(vm.attend_workspace_bytes(d, 1, opts), dtype=torch.uint8, device=dev)
+    torch.cuda.synchronize()
+    if stamp_buffer is not None:
+        vm.stamps_attach(stamp_buffer)
+    try:
+        vm.attend(d, d.window_frames, 1, q_nope, q_r, w_uk, w_uv, c_kv, k_r, out, ws, opts=opts)
+        torch.cuda.synchronize()
+    finally:
+        if stamp_buffer is not None:
+            vm.stamps_attach(None)
+    return out.view(torch.int16).cpu()
+
+
+# (d_c, query tokens, workgroups): the wide-latent kernel
+ATTENDS = {"out_dc512": (512, 0, 0)}
+
+
 def run(vm, stamp_buffer=None):
     """Ring fill of 21 frames, then the chunk-step at frame 21 (packed cache write and the
     attend on the even split) and a batch-4 cache write of the same frames. With

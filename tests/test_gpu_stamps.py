@@ -5,7 +5,8 @@ workgroup in order.
 The binding picks its library at import, so the diagnostic build runs in a child process
 (tests/stamps_child.py) on the same seeded inputs as this process's product run
 (tests/stamps_run.py): one Wan2.1-1.3B chunk-step (packed cache write, attend on the even
-split) and one batch-4 cache write (the wide kernel)."""
+split), one batch-4 cache write (the wide kernel), and an attend of the wide-latent
+kernel."""
 import os
 import subprocess
 import sys
@@ -33,8 +34,9 @@ def vm():
 
 
 def test_stamps_build_matches_product_and_records_in_order(vm, tmp_path):
-    from tests.stamps_run import run
+    from tests.stamps_run import ATTENDS, run, run_attend
     want = run(vm)
+    want.update({name: run_attend(vm, *args) for name, args in ATTENDS.items()})
     env = dict(os.environ, VIDEOMLA_LIBRARY="stamps")
     print("child: tests/stamps_child.py (diagnostic build)", flush=True)
     r = subprocess.run([sys.executable, "-u", os.path.join(ROOT, "tests", "stamps_child.py"),

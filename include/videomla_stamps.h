@@ -52,7 +52,8 @@ extern "C" {
  *   barrier passed (i < 4). The stream's end is read before the step's wait for its tile
  *   loads, and stored only after the barrier, so the wait has no stamp store to drain. At
  *   d_c = 512 a step has two barriers: the points are at the second, and the tile loads are
- *   waited for at the first;
+ *   waited for at the first. Waves without query rows (few queries) only load: their stream
+ *   ends with the issue of their loads;
  *   10 last step done; 11 partial results stored;
  *   12 the first segment's last step done and 13 its partial results issued (every
  *   workgroup); 14 the second segment's first two tiles landed (workgroups with a second

@@ -754,9 +754,18 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
     for (int t = 0; t < n_tiles; ++t) {
       dma_tile(key_begin + (t + 2) * BN, tile[fill]);
       fill = fill == 2 ? 0 : fill + 1;
+      const bool stamped = !DENSE && stamp_step >= 200 && stamp_step < 204;
+      const uint64_t stream_end = stamped ? VMLA_STAMP_NOW() : 0;
       wait_vmcnt<0>();
       __syncthreads();
+      if (stamped) {
+        VMLA_STAMP(a, kStampAttend, 3 + 2 * (stamp_step - 200));
+        VMLA_STAMP_AT(a, kStampAttend, 2 + 2 * (stamp_step - 200), stream_end);
+      }
+      ++stamp_step;
     }
+    if (!DENSE) VMLA_STAMP(a, kStampAttend, 10);
+    if (!DENSE && stamp_seg == 0) VMLA_STAMP(a, kStampAttend, 12);
   } else {
   f32x16 s_a[QB][C::KB], s_b[QB][C::KB];
   if (n_tiles > 0) scores(tile[0], s_a);

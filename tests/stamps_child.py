@@ -27,8 +27,8 @@ EXPECT = {  # kernel: (workgroups, waves, points in the order they are reached)
 }
 
 
-# the latent attention of stamps_run.ATTENDS: 256 workgroups of 4 waves
-EXPECT_ATTENDS = {"out_dc512": (256, 4)}
+# the latent attention of stamps_run.ATTENDS: 256 workgroups of 4 waves, 4 of 8 waves
+EXPECT_ATTENDS = {"out_dc512": (256, 4), "out_few": (4, 8)}
 
 
 def check(rec, name, grid=None):
@@ -49,7 +49,7 @@ def check(rec, name, grid=None):
     if name == "latent_attend":  # workgroups with two segments: the switch, in order
         two = k[:n_wg, :, 14].max(axis=1) > 0
         sw = k[:n_wg][two][:, :waves][:, :, [1, 12, 13, 14, 10, 11]]
-        assert two.sum() > 0 and (sw > 0).all() and (np.diff(sw, axis=2) >= 0).all(), name
+        assert (two.sum() > 0 or grid == (4, 8)) and (sw > 0).all() and (np.diff(sw, axis=2) >= 0).all(), name
         one = k[:n_wg][~two][:, :waves]  # one segment: points 12 and 13 follow its last step
         assert (one[:, :, 12] >= one[:, :, 10]).all() and (one[:, :, 13] >= one[:, :, 12]).all(), name
         print(f"latent_attend: {int(two.sum())} workgroups with two segments, switch points in order")

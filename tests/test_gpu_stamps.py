@@ -5,8 +5,8 @@ workgroup in order.
 The binding picks its library at import, so the diagnostic build runs in a child process
 (tests/stamps_child.py) on the same seeded inputs as this process's product run
 (tests/stamps_run.py): one Wan2.1-1.3B chunk-step (packed cache write, attend on the even
-split), one batch-4 cache write (the wide kernel), and an attend of the wide-latent
-kernel."""
+split), one batch-4 cache write (the wide kernel), and an attend each of the wide-latent kernel and
+of few queries (waves that only load)."""
 import os
 import subprocess
 import sys

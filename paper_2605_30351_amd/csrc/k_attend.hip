@@ -420,8 +420,8 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
 #pragma unroll
     for (int x = 0; x < 8; ++x) bw[x] = __builtin_amdgcn_readfirstlane(bw[x]);
     const int64_t cum = bal_cum(bw, G);
-    u_begin = uniform(floor_div(U * bal_cum(bw, blockIdx.x), cum));
-    u_end = uniform(floor_div(U * bal_cum(bw, blockIdx.x + 1), cum));
+    u_begin = uniform(bal_start_at(bw, cum, U, blockIdx.x));
+    u_end = uniform(bal_start_at(bw, cum, U, blockIdx.x + 1));
     if (a.bal_rec) bal_t0 = __builtin_amdgcn_s_memrealtime();
   } else {
     u_begin = udiv((int64_t)blockIdx.x * U, G);
@@ -441,7 +441,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
   int split = 0;
   if (kt0 > 0)
     split = (int)blockIdx.x -
-            (a.bal_on ? __builtin_amdgcn_readfirstlane(bal_owner_fd(bw, G, U, rbg * T))
+            (a.bal_on ? __builtin_amdgcn_readfirstlane(bal_owner(bw, G, U, rbg * T))
                       : (int)udiv((rbg * T + 1) * G - 1, U));
   u = seg_lo;
   const int row0 = rb * C::ROWS + wave * QB * 32;

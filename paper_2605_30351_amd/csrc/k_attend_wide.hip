@@ -121,8 +121,8 @@ __global__ __launch_bounds__(256, 1) void latent_attend_wide_kernel(const Attend
 #pragma unroll
     for (int x = 0; x < 8; ++x) bw[x] = __builtin_amdgcn_readfirstlane(bw[x]);
     const int64_t cum = bal_cum(bw, G);
-    u_begin = uniform(floor_div(U * bal_cum(bw, blockIdx.x), cum));
-    u_end = uniform(floor_div(U * bal_cum(bw, blockIdx.x + 1), cum));
+    u_begin = uniform(bal_start_at(bw, cum, U, blockIdx.x));
+    u_end = uniform(bal_start_at(bw, cum, U, blockIdx.x + 1));
     if (a.bal_rec) bal_t0 = __builtin_amdgcn_s_memrealtime();
   } else {
     u_begin = uniform(floor_div((int64_t)blockIdx.x * U, G));
@@ -171,8 +171,8 @@ __global__ __launch_bounds__(256, 1) void latent_attend_wide_kernel(const Attend
     int split = 0;
     if (kt0 > 0)
       split = (int)blockIdx.x - __builtin_amdgcn_readfirstlane(
-                                    a.bal_on ? bal_owner_fd(bw, G, U, rbg * T)
-                                             : attend_owner_fd(rbg * T, U, G));
+                                    a.bal_on ? bal_owner(bw, G, U, rbg * T)
+                                             : attend_owner(rbg * T, U, G));
     const int row0 = rb * C::ROWS;
     const int key_begin = kt0 * BN;
     const int key_end = min(a.n_valid, (kt0 + n_tiles) * BN);

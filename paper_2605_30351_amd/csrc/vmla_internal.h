@@ -162,9 +162,22 @@ struct PrepArgs {
   int32_t n_heads, d_model, d_nope, d_rope, d_c, d_v, d_q, d_q_pad, k_out_pad;
 };
 
+// floor(n / d) for n >= 0, d >= 1, exactly, without the integer division's chain of about 150
+// instructions. Below 2^53 both operands are exact doubles, and the truncated, correctly rounded
+// quotient is already floor(n / d): a quotient q + r/d with r >= 1 sits at least 1/d above q and
+// 1/d below q + 1, more than half an ulp of it (at most n 2^-53 / d). The two correction steps only
+// guard against a division that is not correctly rounded.
+__host__ __device__ inline int64_t floor_div(int64_t n, int64_t d) {
+  if (n >= (int64_t(1) << 53)) return n / d;
+  int64_t q = (int64_t)((double)n / (double)d);
+  if (q * d > n) --q;
+  else if ((q + 1) * d <= n) ++q;
+  return q;
+}
+
 // Workgroup whose unit range [w*U/G, (w+1)*U/G) contains `unit`.
 __host__ __device__ inline int attend_owner(int64_t unit, int64_t units, int n_wg) {
-  return (int)(((unit + 1) * (int64_t)n_wg - 1) / units);
+  return (int)floor_div((unit + 1) * (int64_t)n_wg - 1, units);
 }
 
 // The most workgroups that share one of N row blocks of T units each, split evenly over G <= N T:
@@ -250,44 +263,18 @@ __host__ __device__ inline int64_t bal_cum(const uint32_t* w, int k) {
   for (int x = 0; x < 8; ++x) s += (int64_t)w[x] * (k > x ? (k - x + 7) / 8 : 0);
   return s;
 }
+// start(k); cum_g = cum(G)
+__host__ __device__ inline int64_t bal_start_at(const uint32_t* w, int64_t cum_g, int64_t U, int k) {
+  return floor_div(U * bal_cum(w, k), cum_g);
+}
 __host__ __device__ inline int64_t bal_start(const uint32_t* w, int G, int64_t U, int k) {
-  return U * bal_cum(w, k) / bal_cum(w, G);
+  return bal_start_at(w, bal_cum(w, G), U, k);
 }
 // The workgroup whose range contains `unit`: the largest k < G with start(k) <= unit, i.e.
 // with cum(k) <= C = floor(((unit + 1) cum(G) - 1) / U); cum(8q + j) = q S + w[0] + .. + w[j-1]
 // with S the sum of the 8 weights, so k = 8 (C / S) + the number of leading weights whose sum
 // stays within C mod S.
 __host__ __device__ inline int bal_owner(const uint32_t* w, int G, int64_t U, int64_t unit) {
-  const int64_t C = ((unit + 1) * bal_cum(w, G) - 1) / U;
-  int64_t S = 0;
-  for (int x = 0; x < 8; ++x) S += w[x];
-  int64_t r = C % S, k = C / S * 8;
-  for (int x = 0; x < 7 && r >= (int64_t)w[x]; ++x) {
-    r -= w[x];
-    ++k;
-  }
-  return (int)(k < G - 1 ? k : G - 1);
-}
-// floor(n / d) for n >= 0, d >= 1, exactly. Below 2^53 both operands are exact doubles, and
-// the truncated, correctly rounded quotient is already floor(n / d): a quotient q + r/d with
-// r >= 1 sits at least 1/d above q and 1/d below q + 1, more than half an ulp of it (at most
-// n 2^-53 / d). The two correction steps only guard against a division that is not correctly
-// rounded.
-__host__ __device__ inline int64_t floor_div(int64_t n, int64_t d) {
-  if (n >= (int64_t(1) << 53)) return n / d;
-  int64_t q = (int64_t)((double)n / (double)d);
-  if (q * d > n) --q;
-  else if ((q + 1) * d <= n) ++q;
-  return q;
-}
-// attend_owner and bal_owner with their divisions done by floor_div: the same results. The
-// merge kernels compute a row block's split count per thread, where the 64-bit integer
-// division sequence would dominate; the attention kernel keeps the integer forms, whose code
-// its register allocation was tuned with.
-__host__ __device__ inline int attend_owner_fd(int64_t unit, int64_t units, int n_wg) {
-  return (int)floor_div((unit + 1) * (int64_t)n_wg - 1, units);
-}
-__host__ __device__ inline int bal_owner_fd(const uint32_t* w, int G, int64_t U, int64_t unit) {
   // C <= cum(G) <= kBalMax G < 2^32 for the at most 2^20 workgroups of a call; S < 2^14
   const uint32_t C = (uint32_t)floor_div((unit + 1) * bal_cum(w, G) - 1, U);
   uint32_t S = 0;

@@ -1,16 +1,29 @@
-// Host check of the adaptive partition arithmetic of the attention kernel (vmla_internal.h):
-// the closed-form owner against a brute-force scan, the merge kernels' owner forms (divisions
-// by floor_div) against the integer ones and floor_div against integer division, the ranges
-// tiling [0, U) without empty ranges, the equal-weight case against the even split, and the
-// partial-result slot bound.
+// Host check of the adaptive partition arithmetic of the attention kernel (vmla_internal.h), whose
+// divisions go through floor_div: floor_div against integer division, the start of a share and the
+// owner of a unit, even and weighted, against their integer forms here, the closed-form owner
+// against a brute-force scan, the ranges tiling [0, U) without empty ranges, the equal-weight case
+// against the even split, and the partial-result slot bound.
 #include "vmla_internal.h"
 #include <cstdio>
 #include <random>
 using namespace vmla;
 
+int64_t start_int(const uint32_t* w, int G, int64_t U, int k) { return U * bal_cum(w, k) / bal_cum(w, G); }
+int attend_owner_int(int64_t unit, int64_t U, int G) { return (int)(((unit + 1) * (int64_t)G - 1) / U); }
+int bal_owner_int(const uint32_t* w, int G, int64_t U, int64_t unit) {
+  const int64_t C = ((unit + 1) * bal_cum(w, G) - 1) / U;
+  int64_t S = 0;
+  for (int x = 0; x < 8; ++x) S += w[x];
+  int64_t r = C % S, k = C / S * 8;
+  for (int x = 0; x < 7 && r >= (int64_t)w[x]; ++x) {
+    r -= w[x];
+    ++k;
+  }
+  return (int)(k < G - 1 ? k : G - 1);
+}
 int owner_ref(const uint32_t* w, int G, int64_t U, int64_t u) {
   int best = 0;
-  for (int k = 0; k < G; ++k) if (bal_start(w, G, U, k) <= u) best = k;
+  for (int k = 0; k < G; ++k) if (start_int(w, G, U, k) <= u) best = k;
   return best;
 }
 int main() {
@@ -46,10 +59,12 @@ int main() {
       ++checks;
       if (bal_owner(w, G, U, u) != owner_ref(w, G, U, u)) { if (bad++ < 5) printf("bad G=%d U=%ld u=%ld got %d want %d\n", G, (long)U, (long)u, bal_owner(w, G, U, u), owner_ref(w, G, U, u)); }
       if (it % 5 == 0 && bal_owner(w, G, U, u) != (int)(((u + 1) * (int64_t)G - 1) / U)) { if (bad++ < 5) printf("uniform mismatch\n"); }
-      // the merge kernels' forms with the divisions done by floor_div
-      if (bal_owner_fd(w, G, U, u) != bal_owner(w, G, U, u)) { if (bad++ < 5) printf("bal_owner_fd G=%d U=%ld u=%ld\n", G, (long)U, (long)u); }
-      if (attend_owner_fd(u, U, G) != attend_owner(u, U, G)) { if (bad++ < 5) printf("attend_owner_fd G=%d U=%ld u=%ld\n", G, (long)U, (long)u); }
+      // the integer forms
+      if (bal_owner(w, G, U, u) != bal_owner_int(w, G, U, u)) { if (bad++ < 5) printf("bal_owner G=%d U=%ld u=%ld\n", G, (long)U, (long)u); }
+      if (attend_owner(u, U, G) != attend_owner_int(u, U, G)) { if (bad++ < 5) printf("attend_owner G=%d U=%ld u=%ld\n", G, (long)U, (long)u); }
     }
+    for (int k = 0; k <= G; ++k)
+      if (bal_start(w, G, U, k) != start_int(w, G, U, k)) { bad++; printf("bal_start G=%d U=%ld k=%d\n", G, (long)U, k); break; }
     // ranges tile [0, U)
     if (bal_start(w, G, U, 0) != 0 || bal_start(w, G, U, G) != U) { bad++; printf("ends\n"); }
     // bal_max_seg bound

@@ -72,8 +72,8 @@ __device__ __forceinline__ float quad_sum(float v) {
   return half_swap_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 
-template <int DC, int DR>
 struct WideCfg {
+  static constexpr int DC = 512, DR = 32;
   static constexpr int NW = 4, ROWS = kWideRows, BN = kWideKeys, NBUF = 4;
   static constexpr int DQK = DC + DR;
   static constexpr int KS = DQK / 32;            // score steps of 32 columns
@@ -81,16 +81,15 @@ struct WideCfg {
   static constexpr int TILE = BN * DQK;          // elements
   static constexpr int CL = BN / NW;             // c_kv rows (loads) per wave and tile
   static constexpr int RL = BN * DR / 512;       // k_r loads per tile, by waves 0 .. RL-1
-  static_assert(DC == 512 && DR == 32 && RL <= NW && CL == 2 * DB, "one load per c_kv row and value slot");
+  static_assert(RL <= NW && CL == 2 * DB, "one load per c_kv row and value slot");
   // chunk c of row r sits at c ^ swz(r) (k_r rows, of four chunks: c ^ swz4(r))
   static constexpr int swz4(int r) { return -(r >> 2) & 3; }
   static constexpr int swz(int r) { return ((r & 3) << 2) | swz4(r); }
 };
 
-template <int DC, int DR>
 __global__ __launch_bounds__(256, 1) void latent_attend_wide_kernel(const AttendArgs a) {
-  using C = WideCfg<DC, DR>;
-  constexpr int BN = C::BN, DB = C::DB, KS = C::KS;
+  using C = WideCfg;
+  constexpr int DC = C::DC, DR = C::DR, BN = C::BN, DB = C::DB, KS = C::KS;
   __shared__ __attribute__((aligned(16))) uint16_t tile[C::NBUF][C::TILE];
   __shared__ __attribute__((aligned(16))) uint16_t pbuf[2][2][2][32][8];  // [rows/32][kk][g][row][key]
   __shared__ float mx[2][C::ROWS];                                       // [key half][row]
@@ -267,7 +266,7 @@ __global__ __launch_bounds__(256, 1) void latent_attend_wide_kernel(const Attend
     }
     if (key_begin + BN > key_end) mask_tail(key_begin, s_cur);
     put_max(s_cur);
-        // Operands read ahead: 6 score and 3 value operands (4 and 3: 3610 us, 8 and 3: 3740, 6 and 2:
+    // Operands read ahead: 6 score and 3 value operands (4 and 3: 3610 us, 8 and 3: 3740, 6 and 2:
     // 3530, against 3500 at the shape above).
     constexpr int PF = 6, VA = 3;
     bf16x8 kq[PF];
@@ -449,7 +448,7 @@ __global__ __launch_bounds__(256, 1) void latent_attend_wide_kernel(const Attend
 
 hipError_t launch_latent_attend_wide(const AttendArgs& a, hipStream_t s) {
   // validated by the caller: d_c = 512, d_rope = 32, rows and keys per block as in WideCfg
-  hipLaunchKernelGGL((latent_attend_wide_kernel<512, 32>), dim3(a.n_wg), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(latent_attend_wide_kernel, dim3(a.n_wg), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -167,7 +167,7 @@ __global__ __launch_bounds__(256, 1) void dense_cache_write_kernel(const DenseWr
 // every RoPE pair into LDS (K tiles), the rotated bf16 rows into an LDS tile per wave, and 16-byte
 // chunks of whole rows from there to the ring.
 // ---------------------------------------------------------------------------------------------
-using DwTile = GemmTile<4, 2, 2, 4, 32, 4>;
+using DwTile = GemmTile<4, 2, 2, 4, 4>;
 constexpr int kDwCs = kDwMaxPairs + 1;                       // (cos, sin) row stride, padded
 constexpr int kDwOs = DwTile::MO * 32 + 8;                   // output tile row stride (elements)
 constexpr size_t kDwOutBytes = (size_t)DwTile::NW * 32 * kDwOs * 2;
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(DwTile::NT, 1) void dense_cache_write_wide_kernel(c
         return o < hd ? GemmRows{a.w_k + (size_t)o * dm, hd - 1 - o}
                       : GemmRows{a.w_v + (size_t)(o - hd) * dm, N - 1 - o};
       },
-      [](int, bf16x8) {}, acc);
+      acc);
 
   uint16_t* ot = reinterpret_cast<uint16_t*>(smem) + wave * 32 * kDwOs;
   f32x2* cs = reinterpret_cast<f32x2*>(smem + kDwOutBytes);

@@ -3,7 +3,7 @@
 //
 // WT x WO waves, each NB x 32 tokens by MO x 32 outputs. An MFMA takes 32 cycles of its SIMD, in
 // which the compute unit's LDS delivers 1 KB to each of its four SIMDs, the size of one operand
-// block; a wave reads (NB + MO) KB per NB MO MFMAs. The contraction streams through ST stages of KC
+// block; a wave reads (NB + MO) KB per NB MO MFMAs. The contraction streams through ST stages of 32
 // columns (token rows, then weight rows, in 16-byte chunks whose index is XOR-ed with a function of
 // the row, so that the 32-row operand reads are conflict-free), filled ST - 1 stages ahead by direct
 // global-to-LDS loads. Every step's operands are read from LDS one step ahead, those of a stage's
@@ -20,9 +20,10 @@ struct GemmRows {
   int more;
 };
 
-template <int WT_, int WO_, int NB_, int MO_, int KC_, int ST_>
+template <int WT_, int WO_, int NB_, int MO_, int ST_>
 struct GemmTile {
-  static constexpr int WT = WT_, WO = WO_, NB = NB_, MO = MO_, KC = KC_, ST = ST_;
+  static constexpr int WT = WT_, WO = WO_, NB = NB_, MO = MO_, ST = ST_;
+  static constexpr int KC = 32;                     // columns per stage
   static constexpr int NW = WT * WO, NT = NW * 64;
   static constexpr int TT = WT * NB * 32, TO = WO * MO * 32, ROWS = TT + TO;
   static constexpr int CPR = KC / 8;                // chunks per row
@@ -30,18 +31,17 @@ struct GemmTile {
   static constexpr int STAGE = ROWS * KC;           // elements
   static constexpr int KS = KC / 16;                // MFMA steps per stage
   static_assert(ROWS * CPR % (64 * NW) == 0 && LPW % KS == 0, "stage loads split evenly over the waves");
-  static_assert((KC == 64 || KC == 32) && ST >= 3, "stage layout, lookahead");
+  static_assert(ST >= 3, "lookahead");
   // chunk c of row r sits at c ^ swz(r)
-  __device__ static constexpr int swz(int r) { return KC == 64 ? (r >> 1) & 7 : (r >> 2) & 3; }
+  __device__ static constexpr int swz(int r) { return (r >> 2) & 3; }
 
   // acc[nb][m]: tokens 32 (NB wt + nb) .. and outputs 32 (MO wo + m) .. of the tile, wave = wt +
-  // WT wo. group(r) describes the source of the 512 / KC tile rows from r on (tokens 0 .. TT - 1,
-  // then outputs): the first row's pointer and the number of rows that may be read after it (later
-  // ones repeat the last), row stride ld elements. on_b(nb, v) sees every token operand once per
-  // wave. The stages are free again after a barrier.
-  template <class Group, class OnB>
+  // WT wo. group(r) describes the source of the 16 tile rows from r on (tokens 0 .. TT - 1, then
+  // outputs): the first row's pointer and the number of rows that may be read after it (later ones
+  // repeat the last), row stride ld elements. The stages are free again after a barrier.
+  template <class Group>
   __device__ static __forceinline__ void run(uint16_t* stage, int nchunks, int ld, Group&& group,
-                                             OnB&& on_b, f32x16 (&acc)[NB][MO]) {
+                                             f32x16 (&acc)[NB][MO]) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wt = wave % WT, wo = wave / WT;
@@ -105,8 +105,6 @@ struct GemmTile {
         constexpr int ks = decltype(ksc)::value, X = NB * MO, R = NB + MO, D = LPW / KS;
         // the next step's operands; past the last chunk a stale stage, never used
         const uint16_t* st = stage + (ks + 1 < KS ? slot : next) * STAGE;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) on_b(nb, bx[ks & 1][nb]);
         for_const<X>([&](auto xc) {
           constexpr int x = decltype(xc)::value, m = x / NB, nb = x % NB;
           __builtin_amdgcn_sched_barrier(0);

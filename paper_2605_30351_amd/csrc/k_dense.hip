@@ -431,18 +431,12 @@ __global__ __launch_bounds__(256) void dense_merge_split_kernel(const AttendArgs
 
 hipError_t launch_dense_cache_write(const DenseWriteArgs& a, hipStream_t s) {
   // validated by the caller: d_model % 64 == 0, (2 H d_head) % 128 == 0, d_head even
-  const int64_t M = (int64_t)a.batch * a.geo.chunk_tokens, N = 2LL * a.n_heads * a.d_head;
-  const int64_t wide = (M + DwTile::TT - 1) / DwTile::TT * ((N + DwTile::TO - 1) / DwTile::TO);
-  const int64_t small = (int64_t)a.batch * ((a.geo.chunk_tokens + kDwTok - 1) / kDwTok) * (N / kDwOut);
-  // Rounds of one workgroup per compute unit. A round of wide tiles (four times the work) takes
-  // about as long as two of the small ones: 40 to 54 us a round, the fuller the longer, against 25
-  // for one and 20 for each further one at d_model = 1536, 27 to 32 against 18 and 13 at 768
-  // (2 against 1 rounds: 40.2 against 45.2 us at 1,560 tokens x 12 heads, 4 against 1: 83.6
-  // against 52.3 at 3,120 x 16). d_head % 8: the stores' 16-byte chunks stay inside a head.
-  auto rounds = [&](int64_t tiles) { return (tiles + a.n_cu - 1) / a.n_cu; };
-  if (a.d_head % 8 == 0 && a.d_head / 2 <= kDwMaxPairs && rounds(small) > 2 * rounds(wide) &&
-      M + DwTile::TT < (1LL << 31) && wide < (1LL << 31)) {
-    const dim3 grid((unsigned)wide), block(DwTile::NT);
+  static_assert(kDwTok == kDenseTile && kDwOut == kDenseTile, "tile of the rule");
+  static_assert(DwTile::TT == kDenseWideTile && DwTile::TO == kDenseWideTile, "tile of the rule");
+  if (a.d_head / 2 <= kDwMaxPairs &&
+      dense_write_wide(a.batch, a.geo.chunk_tokens, a.n_heads, a.d_head, a.n_cu)) {
+    const int64_t M = (int64_t)a.batch * a.geo.chunk_tokens;
+    const dim3 grid((unsigned)dense_wide_tiles(M, 2LL * a.n_heads * a.d_head)), block(DwTile::NT);
     if (a.d_head == kDwWideHead) hipLaunchKernelGGL(dense_cache_write_wide_kernel<true>, grid, block, 0, s, a);
     else hipLaunchKernelGGL(dense_cache_write_wide_kernel<false>, grid, block, 0, s, a);
     return hipGetLastError();

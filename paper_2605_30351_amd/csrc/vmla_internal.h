@@ -307,6 +307,25 @@ __host__ inline bool weighted_split_fits(const Partition& p, int n_seg) {
   return p.G <= kBalMaxWg && need != kBalNever && need <= n_seg;
 }
 
+// Whether the dense cache write takes its 256 x 256 tiles instead of the 128 x 128 ones. Rounds of
+// one workgroup per compute unit: a round of wide tiles (four times the work) takes about as long
+// as two of the small ones: 40 to 54 us a round, the fuller the longer, against 25 for one and 20
+// for each further one at d_model = 1536, 27 to 32 against 18 and 13 at 768 (2 against 1 rounds:
+// 40.2 against 45.2 us at 1,560 tokens x 12 heads, 4 against 1: 83.6 against 52.3 at 3,120 x 16).
+// d_head % 8: the wide kernel's stores, 16-byte chunks, stay inside a head.
+constexpr int kDenseTile = 128, kDenseWideTile = 256;
+__host__ inline int64_t dense_wide_tiles(int64_t M, int64_t N) {
+  return (M + kDenseWideTile - 1) / kDenseWideTile * ((N + kDenseWideTile - 1) / kDenseWideTile);
+}
+__host__ inline bool dense_write_wide(int64_t batch, int64_t tokens, int64_t n_heads, int64_t d_head,
+                                      int64_t n_cu) {
+  const int64_t M = batch * tokens, N = 2 * n_heads * d_head, wide = dense_wide_tiles(M, N);
+  const int64_t small = batch * ((tokens + kDenseTile - 1) / kDenseTile) * (N / kDenseTile);
+  auto rounds = [&](int64_t tiles) { return (tiles + n_cu - 1) / n_cu; };
+  return d_head % 8 == 0 && rounds(small) > 2 * rounds(wide) && M + kDenseWideTile < (1LL << 31) &&
+         wide < (1LL << 31);
+}
+
 // Whether the partial results of a call of `rows` query rows, each split over up to `splits`
 // workgroups, are merged by a workgroup per row (vmla_merge.h) instead of a thread per 8 columns.
 // While the bytes are few, the first takes about 4 us and 2.5 us per 1,000 rows, whatever the splits;

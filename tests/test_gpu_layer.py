@@ -3,7 +3,9 @@ path into B_h, App. "Inference-Time Reparameterization") through the C ABI, agai
 oracle's training-time layer (explicit per-head queries, keys and values, then W_O) in fp64.
 
 * Tiny shape, d_q = 48 (padded to one 64-column chunk inside the packed weights), batch 2:
-  every output of a 6-frame rollout, with and without a sink frame.
+  every output of a 6-frame rollout, with and without a sink frame; and over a window of 12 key
+  tiles, each taken by a workgroup of its own, so that a workgroup per row merges them into o_lat
+  rows with padding columns (32 of 64), the workspace full of NaN before.
 * Wan shape, d_q = 768 (the paper's query latent), batch 1: the chunk at frame 18 (full
   window), sampled rows.
 
@@ -85,6 +87,18 @@ def test_tiny_layer_rollout(vm, dims):
             want = O.attention_layer(inp, b, fe)
             assert_attention_close(got[b], want, f"tiny layer {dims.sink_frames} fe={fe} b={b}")
         fe = vm.window_advance(dims, fe)
+
+
+def test_tiny_layer_many_splits(vm):
+    d = TINY.replace(window_frames=24)
+    inp = make_full_layer_inputs(d, seed=22, n_frames=25, d_q=48, batch=2)
+    layer = FullLayer(vm, inp)
+    for fe in range(24):
+        vm.cache_write(d, fe, 2, layer.chunk(fe), layer.w_dkv, layer.w_kr, layer.gamma, layer.c_kv, layer.k_r)
+    ws = torch.full((vm.attend_layer_workspace_bytes(d, inp.d_q, 2),), 0xFF, dtype=torch.uint8, device="cuda")
+    got = layer.step(24, ws=ws)
+    for b in range(2):
+        assert_attention_close(got[b], O.attention_layer(inp, b, 24), f"tiny layer, 12 splits, b={b}")
 
 
 def test_wan_layer_full_window(vm):

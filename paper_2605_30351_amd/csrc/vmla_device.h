@@ -68,8 +68,12 @@ __device__ __forceinline__ void lds_dma16(const uint16_t* gptr, uint32_t lds_bas
                : "memory", "m0");
 }
 // The same to LDS address lds_base + LDS_OFF, from a scalar base and the lane offset off + add in
-// bytes: three instructions, of which the sum is also the wait state between the write of m0 and
-// its use. The second form takes the lane offset min(off, lim).
+// bytes; the sum is also the wait state between the write of m0 and its use. The second form takes
+// the lane offset min(off, lim). A vector-memory instruction may read a scalar register five wait
+// states after a VALU instruction (a readfirstlane, or the reload of a spilled one) wrote it; the
+// compiler keeps that distance for its own instructions, not for the one in here, whose base the
+// callers compute well before. tests/test_direct_loads.py checks it in the generated code (three
+// more wait states in here cost the wide-latent attention 1.2%: 3533 against 3574 us).
 template <int LDS_OFF>
 __device__ __forceinline__ void lds_dma16_add(const void* base, uint32_t off, uint32_t add,
                                               uint32_t lds_base) {

@@ -657,7 +657,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
     };
     const lds_u16* vlo = as_lds(cur) + vofs_lo;
     const lds_u16* vhi = as_lds(cur) + vofs_hi;
-    auto vread = [&](int j) {  // A operand of PV MFMA j: kk = j / DVBW, d = j % DVBW
+    auto vread = [&](int j) {  // A operand of PV MFMA j: kk = j / DVB, d = j % DVB
       const int kk = j / C::DVB, d = j % C::DVB;
       if constexpr (DENSE)
         return join_bf16x8(lds_read_tr(as_lds(cur) + vofs_d[0][d] + kk * 16 * C::STRIDE),
@@ -851,9 +851,9 @@ __global__ __launch_bounds__(NW * 64, WPC) void latent_attend_kernel(const Atten
 // wave whose rows have fewer splits runs its MFMAs and stores while the others still load.
 // Lanes of tokens past the chunk work on the chunk's last token and store nothing.
 // PRE (few-query calls, whose few row blocks are split over many workgroups each): steps 1 and
-// 2 are done beforehand by latent_merge_kernel, which runs one thread per (row, 8 columns) over
-// every row at once and leaves the merged bf16 o_lat rows [row][DC] in the q_cat area; the
-// kernel then copies them into its tile and applies W_UV_h.
+// 2 are done beforehand for every row at once, by a workgroup per row or a thread per (row, 8
+// columns) (launch_latent_merge), which leaves the merged bf16 o_lat rows [row][DC] in the q_cat
+// area; the kernel then copies them into its tile and applies W_UV_h.
 // ---------------------------------------------------------------------------------------------
 constexpr int kMergeSplits = 4;
 

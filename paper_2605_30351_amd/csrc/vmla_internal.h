@@ -362,7 +362,7 @@ hipError_t launch_latent_attend(const AttendArgs& a, hipStream_t s);
 hipError_t launch_latent_attend_wide(const AttendArgs& a, hipStream_t s);  // d_c = 512
 constexpr int kWideRows = 64, kWideKeys = 32;  // its row block and key tile
 // out_proj of a call whose row blocks can be split over more workgroups than its in-kernel
-// merge table holds (few-query calls): latent_merge first writes the merged bf16 o_lat rows
+// merge table holds (few-query calls): launch_latent_merge first writes the merged bf16 o_lat rows
 // [row][d_c] into the q_cat area (ld_olat = n_heads * d_c), which out_proj then reads.
 bool out_proj_premerged(const AttendArgs& a);
 hipError_t launch_out_proj(const AttendArgs& a, hipStream_t s);

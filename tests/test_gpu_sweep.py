@@ -1,7 +1,8 @@
 """GPU parity of the paper's d_c sweep (Table 5: latent widths 64, 128, 192, 256 and 512 with
 the 32-wide RoPE key) and of the few-query regime (1-frame chunks), through the C ABI against
-the fp64 oracle. Bars as in tests/test_gpu_parity.py. At d_c = 512 the attention splits the
-value columns over wave pairs and only the packed-weight cache write applies (544 outputs)."""
+the fp64 oracle. Bars as in tests/test_gpu_parity.py. At d_c = 512 the attention has a
+kernel of its own (scores split over four waves by rows and keys, value columns by waves) and only the
+packed-weight cache write applies (544 outputs)."""
 import numpy as np
 import pytest
 import torch

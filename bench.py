@@ -32,8 +32,8 @@ HBM_PEAK_GBPS = 8000.0           # MI355X published HBM3E bandwidth
 ATTEND_TRAFFIC = {"sources": ("paper_2605_30351_amd/csrc/k_attend.hip",
                               "paper_2605_30351_amd/csrc/vmla_device.h",
                               "paper_2605_30351_amd/csrc/vmla_internal.h"),
-                  "sha256": "a47ad6e1a56563d990164ba0c5ef2ddd24ccda38ab5361571a63f588d2140e4c",
-                  "bytes": 307742817}
+                  "sha256": "971f441b7b8d06bea6b4f171ceb8fda6e6ba0a341fc587d1c89f87352540a385",
+                  "bytes": 318264801}
 
 
 def log(msg):

@@ -4,8 +4,9 @@
 //
 // What bounds it: a row's fp32 accumulators (512 columns) leave room for 64 rows per compute unit
 // at one wave per SIMD, and every 32-key tile is read from LDS for those 64 rows only. A 32x32x16
-// MFMA whose A operand is read for 32 rows takes 1 KB of LDS per 32 cycles and SIMD, the whole
-// 128 B per cycle that LDS delivers; so the split is chosen for the fewest LDS bytes:
+// MFMA whose A operand is read for 32 rows takes 1 KB of LDS per 32 cycles and SIMD, half of what
+// LDS delivers (256 B per cycle, in 16-byte and in transposed reads alike, measured), and the one
+// wave of a SIMD has nothing to run while it waits; so the split is chosen for the fewest LDS bytes:
 //   scores   wave (r, k) takes the rows 32 r .. +32 and the keys 16 k .. +16 of the tile, over all
 //            columns (MFMA 16x16x32, the K operand shared by two 16-row blocks): 17 KB;
 //   P^T      goes through LDS as bf16 (4 KB per tile), so that every score is computed and
@@ -15,7 +16,7 @@
 // 30 KB per wave and tile. The version before (pairs of waves that each contracted half of the
 // columns for 32 rows, exchanged fp32 partial scores and both exponentiated them) read and wrote
 // 41 KB. Wan chunk of 4,680 tokens x 12 heads over 32,760 keys, whole attend: 4720 us before, 3500
-// now (1.11 PFLOP/s). The matrix pipes are busy 46% of the cycles at 2.0 GHz; what is left is the
+// now (1.11 PFLOP/s). The matrix pipes are busy 48% of the cycles at 2.0 GHz; what is left is the
 // 35 KB of tile that every compute unit takes in per 64 rows (without these loads: 3050 us).
 //
 // A step t runs the score MFMAs of tile t+1 with the softmax of tile t under them, a barrier that

@@ -155,9 +155,9 @@ __global__ __launch_bounds__(256, 1) void dense_cache_write_kernel(const DenseWr
 // waves of 64 x 128), the tokens flat over the batch. Tiles are numbered token-block-major and
 // dealt to the XCDs in contiguous ranges, so that the tiles of an XCD's L2 share their token rows
 // and the weights.
-// What bounds it: the 128 x 128 tile of the kernel above reads 1.25 KB of LDS per MFMA, more than
-// the LDS delivers in its 32 cycles, takes in twice the bytes per product, and its four waves wait
-// for every stage together. Here an MFMA takes 0.75 KB, and every operand is read a step ahead.
+// What bounds it: the 128 x 128 tile of the kernel above reads 1.25 KB of LDS per MFMA, of the 2 KB
+// that LDS delivers in its 32 cycles, takes in twice the bytes per product, and its four waves, one
+// per SIMD, wait for every stage together. Here an MFMA takes 0.75 KB, and every operand is read a step ahead.
 // 18,720 tokens x 3,072 outputs x 1,536: 307 us with the small tiles, 202 now (875 TFLOP/s; 888
 // tiles are 3.5 rounds of 256). With the MFMAs alone 123 us, without the tile loads 161, without
 // the LDS reads 174, without the epilogue 165: the parts share the chip's power more than its

@@ -2,8 +2,8 @@
 // tile per workgroup with MFMA 32x32x16 (A = weight rows, B = token rows).
 //
 // WT x WO waves, each NB x 32 tokens by MO x 32 outputs. An MFMA takes 32 cycles of its SIMD, in
-// which the compute unit's LDS delivers 1 KB to each of its four SIMDs, the size of one operand
-// block; a wave reads (NB + MO) KB per NB MO MFMAs. The contraction streams through ST stages of 32
+// which the compute unit's LDS delivers 2 KB to each of its four SIMDs, the size of two operand
+// blocks; a wave reads (NB + MO) KB per NB MO MFMAs. The contraction streams through ST stages of 32
 // columns (token rows, then weight rows, in 16-byte chunks whose index is XOR-ed with a function of
 // the row, so that the 32-row operand reads are conflict-free), filled ST - 1 stages ahead by direct
 // global-to-LDS loads. Every step's operands are read from LDS one step ahead, those of a stage's

@@ -578,7 +578,8 @@ int check_materialized_shape(const videomla_dims* d) {
 // with d_k = d_nope + d_rope; multiply-adds per score, bytes, seconds. The constants are a
 // least-squares fit to the two forms' attend times measured on MI355X at the Wan geometry over
 // d_nope 96 / 128, d_c 128 / 192 and 208, 1,560 and 4,680 query tokens (batch 1, 32,760 keys);
-// with them the model picks the faster form at all twelve points.
+// with them the model picks the faster form at all twelve points. Small windows and batches were
+// not fitted: a whole latent attend of a few tiles takes half of kLatentFixed.
 constexpr double kLatentFixed = 67.8e-6;     // seconds: query absorption, merge, pipeline fill
 constexpr double kLatentMacRate = 6.24e14;   // multiply-adds per second, latent attention
 constexpr double kMatFixed = 56.3e-6;        // seconds: query preparation, merge, pipeline fill

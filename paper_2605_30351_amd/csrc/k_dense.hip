@@ -157,12 +157,13 @@ __global__ __launch_bounds__(256, 1) void dense_cache_write_kernel(const DenseWr
 // and the weights.
 // What bounds it: the 128 x 128 tile of the kernel above reads 1.25 KB of LDS per MFMA, of the 2 KB
 // that LDS delivers in its 32 cycles, takes in twice the bytes per product, and its four waves, one
-// per SIMD, wait for every stage together. Here an MFMA takes 0.75 KB, and every operand is read a step ahead.
+// per SIMD, wait for every stage together. Here an MFMA takes 0.75 KB, and every operand is read a
+// step ahead.
 // 18,720 tokens x 3,072 outputs x 1,536: 307 us with the small tiles, 202 now (875 TFLOP/s; 888
 // tiles are 3.5 rounds of 256). In copies with a part taken out: the MFMAs alone 123 us, without the
-// tile loads 161, without the LDS reads 174, without the epilogue 165: the parts share the chip's power more than its
-// cycles. Four waves of 128 x 128 (half the LDS bytes per MFMA): 266 us, 64-column stages with two
-// in flight: 227.
+// tile loads 161, without the LDS reads 174, without the epilogue 165: the parts share the chip's
+// power more than its cycles. Four waves of 128 x 128 (half the LDS bytes per MFMA): 266 us,
+// 64-column stages with two in flight: 227.
 // The epilogue takes 32 of each wave's 64 tokens at a time: the (cos, sin) of those 128 tokens and
 // every RoPE pair into LDS (K tiles), the rotated bf16 rows into an LDS tile per wave, and 16-byte
 // chunks of whole rows from there to the ring.

@@ -2,7 +2,8 @@
 waves without query rows only load (from one row, through whole waves and a wave cut short, to one
 idle wave and none), and the merge of rows split over many workgroups (10 partial results of a row
 by a workgroup, at the latent widths from 64 on, 16 with 12 of them in tests/test_gpu_layer.py, 5 to 10
-in the per-head forms; fewer take the other merge), and its second pass (63 partial results at d_c = 512, where four slices of eight take 32 at a time)."""
+in the per-head forms; fewer take the other merge), and its second pass (63 partial results at
+d_c = 512, where four slices of eight take 32 at a time)."""
 import numpy as np
 import pytest
 import torch
